@@ -10,6 +10,7 @@ constexpr int kMaxWords = 8;  // 32-bit words of q (<= 4 * 54 bits) plus carry r
 
 struct PrimeSet {
   Prime p[kMaxLimbs];
+  int pm;  // every prime is 2^54 - delta with pm_delta() != 0: the transforms' PM form
 };
 
 // Constants of the exact CRT decode.  M_l = q / q_l as 32-bit words.
@@ -24,7 +25,8 @@ struct DecodeConst {
   int words;                           // words used by q and the sums
 };
 
-// Twiddle tables of one limb (pairs of value and Shoup companion): N forward
+// Twiddle tables of one limb (pairs of value and Shoup companion, or the words
+// of pm_pair when every prime of the set allows it): N forward
 // pairs psi_rev, then N inverse stage pairs (entry 2^p + m = omega^-(m N /
 // 2^(p+1)), entry 0 unused), then N final factors psi^-j N^-1.
 struct TwSet {

@@ -18,9 +18,18 @@ namespace sanns {
 // helpers
 // --------------------------------------------------------------------------
 
+// A value that is one per wavefront, as a scalar (divisions are computed per
+// lane, and what they give is not taken for uniform by itself).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // General product of two residues (Karatsuba on 27-bit halves, then the
-// same fold as the multiply-accumulate).
+// same fold as the multiply-accumulate); PM: q = 2^54 - delta.
+template <bool PM = false>
 __device__ __forceinline__ uint64_t mulmod(uint64_t a, uint64_t b, const Prime& P) {
+  if constexpr (PM) {
+    const uint32_t pd = pm_delta(P.q);
+    return reduce_pm60(mulmod_pm(a, b, pd), pd, P.q);
+  }
   uint32_t a0, a1, b0, b1;
   split27(a, a0, a1);
   split27(b, b0, b1);
@@ -35,7 +44,8 @@ __device__ __forceinline__ uint64_t mulmod(uint64_t a, uint64_t b, const Prime& 
 // forward / inverse transforms of independent polynomials
 // --------------------------------------------------------------------------
 
-// Forward transform of polynomial p (limb p % L) by one workgroup.  Output
+// Forward transforms by one workgroup of NP polynomials of one limb, p and p +
+// L (NP = 2: the two components of one ciphertext, p = (e 2 L + l)).  Output
 // forms (split):
 //   0  uint64 residues, polynomial-major like the input;
 //   1  27-bit halves (uint2), polynomial-major: the form the 64-bit
@@ -44,74 +54,83 @@ __device__ __forceinline__ uint64_t mulmod(uint64_t a, uint64_t b, const Prime& 
 //      r = 2q + c (R = 2Q) for polynomial p = ((q d + i) 2 + c) L + l: each
 //      32-slot group of a row is one contiguous block over the coordinates,
 //      the form the digit transpose of the matrix-core schedule reads.
-template <int LOGN, int SPLIT, bool PM = false>
+template <int LOGN, int SPLIT, bool PM, int NP>
 __device__ __forceinline__ void ntt_fwd_poly(int p, int tid, uint64_t* lds,
                                              const uint64_t* __restrict__ in,
                                              uint64_t* __restrict__ out, int L,
                                              const PrimeSet& ps, const TwSet& tws,
                                              uint32_t* err, int d = 0, int R = 0) {
   constexpr int N = NttShape<LOGN>::N;
-  const int l = p % L;
+  const int l = uniform(p % L);
   const Prime& P = ps.p[l];
-  const uint64_t* src = in + (size_t)p * N;
-  uint64_t v[16];
+  uint64_t v[NP][16];
   bool bad = false;
 #pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    v[a] = __builtin_nontemporal_load(src + coef_index<LOGN>(tid, a));  // read once
-    bad |= v[a] >= P.q;
-  }
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a)
+      v[j][a] = __builtin_nontemporal_load(
+          coef_ptr<LOGN, PM>(in + (size_t)(p + j * L) * N, tid, a));  // read once
+#pragma unroll
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a) bad |= v[j][a] >= P.q;
   if (bad && err) atomicOr(err, 1u);
-  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
-  uint64_t* dst = out + (size_t)p * N;
-  if constexpr (SPLIT == 2) {
-    const int c = (p / L) & 1, i = (p / (2 * L)) % d, q = p / (2 * L * d);
-    uint64_t* base = out + (((size_t)l * R + 2 * q + c) * (N / 32) * d + i) * 32;
+  ntt_fwd<LOGN, PM, NP>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      const int s = ntt_slot<LOGN>(tid, a);
-      // read once, by the digit transpose
-      __builtin_nontemporal_store(v[a], base + (size_t)(s >> 5) * d * 32 + (s & 31));
+  for (int j = 0; j < NP; ++j) {
+    const int pj = p + j * L;
+    uint64_t* dst = out + (size_t)pj * N;
+    if constexpr (SPLIT == 2) {
+      const int c = (pj / L) & 1, i = (pj / (2 * L)) % d, q = pj / (2 * L * d);
+      uint64_t* base = out + (((size_t)l * R + 2 * q + c) * (N / 32) * d + i) * 32;
+#pragma unroll
+      for (int a = 0; a < 16; ++a) {
+        const int s = ntt_slot<LOGN>(tid, a);
+        // read once, by the digit transpose
+        __builtin_nontemporal_store(v[j][a], base + (size_t)(s >> 5) * d * 32 + (s & 31));
+      }
+    } else if constexpr (SPLIT == 1) {
+#pragma unroll
+      for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[j][a]);
+    } else {
+#pragma unroll
+      for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = v[j][a];
     }
-  } else if constexpr (SPLIT == 1) {
-    uint2* dst2 = reinterpret_cast<uint2*>(dst);
-#pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      uint2 y;
-      split27(v[a], y.x, y.y);
-      dst2[ntt_slot<LOGN>(tid, a)] = y;
-    }
-  } else {
-#pragma unroll
-    for (int a = 0; a < 16; ++a) dst[ntt_slot<LOGN>(tid, a)] = v[a];
   }
 }
 
-// Waves per SIMD the transform kernels are compiled for: the largest of 4,
-// 6 and 8 at which the compiler fits them in registers without spilling
-// (checked for every log2 N).  The forward needs 64-72 registers; at eight
-// waves (64 registers) the digit form fits except for log2 N = 8, 9 and 14,
-// the other forms do not.  The inverse with the mask takes up to 128
-// registers at four waves and 75-80 at six, where it spills for log2 N = 9,
-// 11, 12 and 14 (9 spills at four waves too, so it keeps six).
-constexpr int ntt_fwd_waves(int logn, int split) {
+// Waves per SIMD that the transform kernels are compiled for.  One polynomial
+// per workgroup: the largest of 4, 6 and 8 at which no form spills for that
+// log2 N.  A pair holds 32 residues per thread (about 104 registers), four
+// waves, which is also what two workgroups of whole-word exchange buffers (70
+// KB each at N = 8192) leave of a CU.
+constexpr int ntt_fwd_waves(int logn, int split, int np) {
+  if (np == 2) return 4;
   return split == 2 && logn != 8 && logn != 9 && logn != 14 ? 8 : 6;
 }
-constexpr int intt_mask_waves(int logn) {
-  return logn == 11 || logn == 12 || logn == 14 ? 4 : 6;
+constexpr int intt_mask_waves(int logn, int np) {
+  return np == 2 || logn == 11 || logn == 12 || logn == 14 ? 4 : 6;
 }
 
-// One polynomial per workgroup (PM: every prime is 2^54 - delta, delta < 2^22).
-template <int LOGN, int SPLIT, bool PM = false>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT))
+// NP = 1: one polynomial per workgroup.  NP = 2: both components of one
+// (ciphertext, limb), which share every twiddle (15 16-byte words per lane in
+// each of the last two passes, more than the 16 residues themselves) and whose
+// independent products interleave.  With the PM products at N = 8192, 64
+// queries of 128 coordinates: 1.63 ms (3.9 TB/s in and out), against 2.16 ms
+// one polynomial at a time and 1.98 ms for the general products.
+template <int LOGN, int SPLIT, int NP, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT, NP))
 k_ntt_fwd(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int L, PrimeSet ps,
           TwSet tws, uint32_t* err, int d, int R) {
   extern __shared__ uint64_t lds[];
-  ntt_fwd_poly<LOGN, SPLIT, PM>(blockIdx.x, threadIdx.x, lds, in, out, L, ps, tws, err, d, R);
+  const int b = blockIdx.x;
+  ntt_fwd_poly<LOGN, SPLIT, PM, NP>(NP == 2 ? uniform(b / L * 2 * L + b % L) : b, threadIdx.x, lds, in,
+                                    out, L, ps, tws, err, d, R);
 }
 
 // In-place inverse transform, result multiplied by N^-1 and in [0, q).
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_ntt_inv(uint64_t* __restrict__ io, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
@@ -123,7 +142,7 @@ k_ntt_inv(uint64_t* __restrict__ io, int L, PrimeSet ps, TwSet tws) {
   uint64_t v[16];
 #pragma unroll
   for (int a = 0; a < 16; ++a) v[a] = buf[ntt_slot<LOGN>(tid, a)];
-  ntt_inv<LOGN>(v, lds, tid, tws.tw[l] + N, P);
+  ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
   __syncthreads();  // every thread has read its inputs before any overwrite
 #pragma unroll
   for (int a = 0; a < 16; ++a) buf[coef_index<LOGN>(tid, a)] = v[a];
@@ -143,6 +162,14 @@ __device__ __forceinline__ void work_pair(const uint32_t* work, int m, int C, in
   }
 }
 
+// The same for an m that is one per workgroup: scalars, for uniform addresses.
+__device__ __forceinline__ void work_pair_uniform(const uint32_t* work, int m, int C, int& qi,
+                                                  int& k) {
+  work_pair(work, m, C, qi, k);
+  qi = uniform(qi);
+  k = uniform(k);
+}
+
 // Thread per (output m, block b).
 __global__ void __launch_bounds__(256)
 k_masks(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restrict__ work,
@@ -160,9 +187,10 @@ k_masks(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restrict
 // inverse transform of the products plus the norm-and-mask plaintext
 // --------------------------------------------------------------------------
 
-// Polynomial p = (m 2 + c) L + l of ct_out: INTT, times N^-1, and for c = 0
-// add Delta_l [norm - r]_t at every coefficient.
-template <int LOGN>
+// Polynomials p and (NP = 2: both components of output m) p + L of ct_out, p =
+// (m 2 + c) L + l: INTT, times N^-1, and for c = 0 add Delta_l [norm - r]_t at
+// every coefficient (PM: both terms are added lazily and reduced once).
+template <int LOGN, bool PM, int NP>
 __device__ __forceinline__ void intt_mask_poly(int p, int tid, uint64_t* lds,
                                                uint64_t* __restrict__ ct,
                                                const uint32_t* __restrict__ share,
@@ -170,59 +198,71 @@ __device__ __forceinline__ void intt_mask_poly(int p, int tid, uint64_t* lds,
                                                const uint32_t* __restrict__ work, int C, int L,
                                                uint32_t t, const PrimeSet& ps, const TwSet& tws) {
   constexpr int N = NttShape<LOGN>::N;
-  const int l = p % L, c = (p / L) & 1, m = p / (2 * L);
+  const int l = uniform(p % L), c = uniform((p / L) & 1), m = uniform(p / (2 * L));
   const Prime& P = ps.p[l];
   uint64_t* buf = ct + (size_t)p * N;
-  uint64_t v[16];
+  uint64_t v[NP][16];
 #pragma unroll
-  for (int a = 0; a < 16; ++a) v[a] = __builtin_nontemporal_load(buf + ntt_slot<LOGN>(tid, a));
-  ntt_inv<LOGN>(v, lds, tid, tws.tw[l] + N, P);
-  if (c == 0) {
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a)
+      v[j][a] = __builtin_nontemporal_load(ntt_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a));
+  ntt_inv<LOGN, PM, true, NP>(v, lds, tid, tws.tw[l] + N, P);
+  if (NP == 2 || c == 0) {
     int qi, k;
-    work_pair(work, m, C, qi, k);
+    work_pair_uniform(work, m, C, qi, k);
     const uint32_t* nrm = norms + (size_t)k * N;
     const uint32_t* r = share + (size_t)m * N;
+    const PmConst pc = pm_const(P.q);
 #pragma unroll
     for (int a = 0; a < 16; ++a) {
-      const int j = coef_index<LOGN>(tid, a);
-      const uint32_t pn = nrm[j], rj = r[j];
-      const uint64_t mv = pn >= rj ? pn - rj : pn + t - rj;
-      v[a] = addmod(v[a], shoup(mv, P.delta, P.deltap, P.q), P.q);
+      const uint32_t pn = *coef_ptr<LOGN, PM>(nrm, tid, a), rj = *coef_ptr<LOGN, PM>(r, tid, a);
+      const uint32_t mv = pn >= rj ? pn - rj : pn + t - rj;
+      if constexpr (PM)
+        v[0][a] += mul_pm32(mv, P.delta, pc);
+      else
+        v[0][a] = addmod(v[0][a], shoup(mv, P.delta, P.deltap, P.q), P.q);
     }
   }
   __syncthreads();  // every thread has read its inputs before any overwrite
+  const uint32_t pd = pm_delta(P.q);
 #pragma unroll
-  for (int a = 0; a < 16; ++a) __builtin_nontemporal_store(v[a], buf + coef_index<LOGN>(tid, a));
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      if constexpr (PM) v[j][a] = reduce_pm60(v[j][a] + 2 * P.q, pd, P.q);
+      __builtin_nontemporal_store(v[j][a], coef_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a));
+    }
 }
 
-// The polynomial of ct_out that workgroup b of a grid of 8 ceil(n / 8) takes
-// (n = 2 L M polynomials; -1 for the grid's padding).  Consecutive blocks go
-// to the eight XCDs in turn, so block b is the (b / 8)-th of XCD b % 8, and
-// each XCD takes a contiguous range of this order: for all pairs (Qa > 0
-// queries, M = Qa C) chunk-major, the outputs of one chunk for every query
-// back to back, so that the chunk's norms are fetched once into that XCD's
-// L2; and the 2L polynomials of an output adjacent, so that the L that read
-// its mask row find it there.  A work list (Qa = 0) keeps its own order.
+// The output polynomials (NP = 1: polynomial p; NP = 2: both components of
+// output m at limb l, returned as the first's p = m 2 L + l) that workgroup b
+// of a grid of 8 ceil(n / 8) takes (n of them; -1 for the grid's padding).
+// Consecutive blocks go to the eight XCDs in turn, so block b is the (b /
+// 8)-th of XCD b % 8, and each XCD takes a contiguous range of this order: for
+// all pairs (Qa > 0 queries, M = Qa C) chunk-major, the outputs of one chunk
+// for every query back to back, so that the chunk's norms are fetched once
+// into that XCD's L2; and the polynomials of an output adjacent, so that those
+// that read its mask row find it there.  A work list (Qa = 0) keeps its own
+// order.
+template <int NP>
 __device__ __forceinline__ int intt_poly_of_block(int b, int n, int Qa, int C, int L) {
-  const int per = (n + 7) >> 3;
+  const int per = (n + 7) >> 3, W = NP == 2 ? L : 2 * L;
   const int idx = (b & 7) * per + (b >> 3);
   if (idx >= n) return -1;
-  if (Qa <= 0) return idx;
-  const int l = idx % L, c = (idx / L) & 1, r = idx / (2 * L);
-  return (((r % Qa) * C + r / Qa) * 2 + c) * L + l;
+  const int r = idx / W;
+  return uniform((Qa <= 0 ? r : (r % Qa) * C + r / Qa) * 2 * L + idx % W);
 }
 
-// At N = 8192: six waves per SIMD (78 registers, three workgroups of 512
-// threads per CU) run 8% faster than four (126 registers, two workgroups).
-template <int LOGN>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN))
+template <int LOGN, int NP, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, NP))
 k_intt_mask(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
             const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
             int L, uint32_t t, PrimeSet ps, TwSet tws, int n, int Qa) {
   extern __shared__ uint64_t lds[];
-  const int p = intt_poly_of_block(blockIdx.x, n, Qa, C, L);
+  const int p = intt_poly_of_block<NP>(blockIdx.x, n, Qa, C, L);
   if (p < 0) return;
-  intt_mask_poly<LOGN>(p, threadIdx.x, lds, ct, share, norms, work, C, L, t, ps, tws);
+  intt_mask_poly<LOGN, PM, NP>(p, threadIdx.x, lds, ct, share, norms, work, C, L, t, ps, tws);
 }
 
 // --------------------------------------------------------------------------
@@ -275,7 +315,7 @@ __device__ __forceinline__ uint64_t flood_residue(const uint32_t* w, int b, uint
 // Workgroup per (output m, limb l): u in NTT form (generated cooperatively
 // into LDS, then transformed), times the NTT form of the query's public key,
 // added to both NTT-form components of ct_out.
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_rerand(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restrict__ work, int C,
          int L, const uint64_t* __restrict__ pk_ntt, uint64_t* __restrict__ ct, PrimeSet ps,
@@ -297,9 +337,9 @@ k_rerand(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restric
   const Prime& P = ps.p[l];
   uint64_t v[16];
 #pragma unroll
-  for (int a = 0; a < 16; ++a) v[a] = lift_small(ub[coef_index<LOGN>(tid, a)], P.q);
+  for (int a = 0; a < 16; ++a) v[a] = lift_coef<PM>(ub[coef_index<LOGN>(tid, a)], P.q);
   __syncthreads();  // the transform reuses the LDS
-  ntt_fwd<LOGN>(v, lds, tid, tws.tw[l], P);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
   const uint64_t* pk0 = pk_ntt + ((size_t)(2 * qi) * L + l) * N;
   const uint64_t* pk1 = pk_ntt + ((size_t)(2 * qi + 1) * L + l) * N;
   uint64_t* c0 = ct + ((size_t)(2 * m) * L + l) * N;
@@ -307,8 +347,14 @@ k_rerand(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restric
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
     const int w = ntt_slot<LOGN>(tid, a);
-    c0[w] = addmod(c0[w], mulmod(v[a], pk0[w], P), P.q);
-    c1[w] = addmod(c1[w], mulmod(v[a], pk1[w], P), P.q);
+    if constexpr (PM) {
+      const uint32_t pd = pm_delta(P.q);
+      c0[w] = reduce_pm60(c0[w] + mulmod_pm(v[a], pk0[w], pd), pd, P.q);
+      c1[w] = reduce_pm60(c1[w] + mulmod_pm(v[a], pk1[w], pd), pd, P.q);
+    } else {
+      c0[w] = addmod(c0[w], mulmod(v[a], pk0[w], P), P.q);
+      c1[w] = addmod(c1[w], mulmod(v[a], pk1[w], P), P.q);
+    }
   }
 }
 
@@ -354,43 +400,62 @@ k_cp_noise(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restr
 
 // k_intt_mask with the re-randomisation's coefficient-form terms (drawn by
 // k_cp_noise): e1, the flood and Delta [norm - r]_t on c0, e2 on c1.
-template <int LOGN>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN))
+template <int LOGN, int NP, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, NP))
 k_intt_mask_cp(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
                const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
                int L, uint32_t t, const uint64_t* __restrict__ flood,
                const int8_t* __restrict__ errs, PrimeSet ps, TwSet tws, int n, int Qa) {
   extern __shared__ uint64_t lds[];
   constexpr int N = NttShape<LOGN>::N;
-  const int tid = threadIdx.x, p = intt_poly_of_block(blockIdx.x, n, Qa, C, L);
+  const int tid = threadIdx.x, p = intt_poly_of_block<NP>(blockIdx.x, n, Qa, C, L);
   if (p < 0) return;
-  const int l = p % L, c = (p / L) & 1, m = p / (2 * L);
+  const int l = uniform(p % L), c0 = uniform((p / L) & 1), m = uniform(p / (2 * L));
   const Prime& P = ps.p[l];
   uint64_t* buf = ct + (size_t)p * N;
-  uint64_t v[16];
+  uint64_t v[NP][16];
 #pragma unroll
-  for (int a = 0; a < 16; ++a) v[a] = buf[ntt_slot<LOGN>(tid, a)];
-  ntt_inv<LOGN>(v, lds, tid, tws.tw[l] + N, P);
-  const int8_t* e = errs + ((size_t)m * 2 + c) * N;
+  for (int j = 0; j < NP; ++j)
 #pragma unroll
-  for (int a = 0; a < 16; ++a) v[a] = addmod(v[a], lift_small(e[coef_index<LOGN>(tid, a)], P.q), P.q);
-  if (c == 0) {
-    int qi, k;
-    work_pair(work, m, C, qi, k);
-    const uint32_t* nrm = norms + (size_t)k * N;
-    const uint32_t* r = share + (size_t)m * N;
-    const uint64_t* fl = flood + ((size_t)m * L + l) * N;
+    for (int a = 0; a < 16; ++a) v[j][a] = *ntt_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a);
+  ntt_inv<LOGN, PM, true, NP>(v, lds, tid, tws.tw[l] + N, P);
+  int qi, k;
+  work_pair_uniform(work, m, C, qi, k);
+  const uint32_t* nrm = norms + (size_t)k * N;
+  const uint32_t* r = share + (size_t)m * N;
+  const uint64_t* fl = flood + ((size_t)m * L + l) * N;
+  const PmConst pc = pm_const(P.q);
+  const uint32_t pd = pm_delta(P.q);
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    const int8_t* e = errs + ((size_t)m * 2 + c0 + j) * N;
 #pragma unroll
     for (int a = 0; a < 16; ++a) {
-      const int j = coef_index<LOGN>(tid, a);
-      const uint32_t pn = nrm[j], rj = r[j];
-      const uint64_t mv = pn >= rj ? pn - rj : pn + t - rj;
-      v[a] = addmod(addmod(v[a], shoup(mv, P.delta, P.deltap, P.q), P.q), fl[j], P.q);
+      const int x = e[coef_index<LOGN>(tid, a)];
+      v[j][a] = PM ? v[j][a] + (uint64_t)(int64_t)x : addmod(v[j][a], lift_small(x, P.q), P.q);
+    }
+  }
+  if (NP == 2 || c0 == 0) {
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      const int jj = coef_index<LOGN>(tid, a);
+      const uint32_t pn = nrm[jj], rj = r[jj];
+      const uint32_t mv = pn >= rj ? pn - rj : pn + t - rj;
+      const uint64_t fj = fl[jj];
+      if constexpr (PM)
+        v[0][a] += mul_pm32(mv, P.delta, pc) + fj;
+      else
+        v[0][a] = addmod(addmod(v[0][a], shoup(mv, P.delta, P.deltap, P.q), P.q), fj, P.q);
     }
   }
   __syncthreads();  // every thread has read its inputs before any overwrite
 #pragma unroll
-  for (int a = 0; a < 16; ++a) buf[coef_index<LOGN>(tid, a)] = v[a];
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a) {
+      if constexpr (PM) v[j][a] = reduce_pm60(v[j][a] + 2 * P.q, pd, P.q);
+      *coef_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a) = v[j][a];
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -1013,7 +1078,7 @@ __device__ bool wait_at_least(uint32_t* ctrl, int idx, uint32_t target, uint32_t
 // A block publishes how many items of a phase it finished (one device-wide
 // release) when it leaves the phase, and waits (one acquire) for the counts
 // a phase depends on when it enters it.
-template <int LOGN, int QT, int CT, int QG, int CG, int DI, int TQT, int TCT>
+template <int LOGN, int QT, int CT, int QG, int CG, int DI, int TQT, int TCT, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
   constexpr int T = NttShape<LOGN>::T, N = NttShape<LOGN>::N;
@@ -1034,10 +1099,10 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
     __syncthreads();
     if (tid == 0) s_ticket = (int)atomicAdd(ctrl + kTicket1, 1u);
     __syncthreads();
-    const int tk = s_ticket;
+    const int tk = uniform(s_ticket);
     if (tk >= n1) break;
     if (tk < n_ntt) {
-      ntt_fwd_poly<LOGN, 1>(tk, tid, lds, A.ct_in, A.qntt, L, ps, tws, A.err);
+      ntt_fwd_poly<LOGN, 1, PM, 1>(tk, tid, lds, A.ct_in, A.qntt, L, ps, tws, A.err);
       ++done_ntt;
     } else {
       const int m = tk - n_ntt;
@@ -1117,9 +1182,9 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
     __syncthreads();
     if (tid == 0) s_ticket = (int)atomicAdd(ctrl + kTicket3, 1u);
     __syncthreads();
-    const int tk = s_ticket;
+    const int tk = uniform(s_ticket);
     if (tk >= n3) break;
-    intt_mask_poly<LOGN>(tk, tid, lds, A.ct_out, A.share, A.norms, A.work, A.C, L, A.t, ps, tws);
+    intt_mask_poly<LOGN, PM, 1>(tk, tid, lds, A.ct_out, A.share, A.norms, A.work, A.C, L, A.t, ps, tws);
   }
 }
 
@@ -1216,34 +1281,33 @@ k_gather32(const void* __restrict__ pts, int kind, long n, int d,
   norms[base + g] = nrm;
 }
 
-// Workgroup per (l, k, i) with k in [k0, k0 + nk): lift the signed
-// plaintext row mod q_l, forward NTT, store as 27-bit halves.
-template <int LOGN, typename G>
+// Workgroup per (limb, NP consecutive rows (k, i)) with k in [k0, k0 + nk):
+// lift the signed plaintext rows mod q_l, forward NTT, store as 27-bit halves
+// (an odd last row is paired with itself and stored once).
+template <int LOGN, typename G, int NP, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_encode_ntt(const G* __restrict__ gt, uint2* __restrict__ dbres, int k0, int nk, int C,
              int d, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
   constexpr int N = NttShape<LOGN>::N;
   const int tid = threadIdx.x;
-  const long bl = blockIdx.x;  // (l nk + k - k0) d + i
-  const int l = (int)(bl / ((long)nk * d));
-  const long ki = bl % ((long)nk * d);
-  const long b = ((long)l * C + k0) * d + ki;
+  const int rows = nk * d, per = (rows + NP - 1) / NP;
+  const int l = uniform((int)blockIdx.x / per), r0 = uniform(NP * ((int)blockIdx.x % per));
   const Prime& P = ps.p[l];
-  const G* src = gt + (size_t)ki * N;
-  uint64_t v[16];
+  uint64_t v[NP][16];
 #pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    const int64_t x = src[coef_index<LOGN>(tid, a)];
-    v[a] = x < 0 ? P.q - (uint64_t)(-x) : (uint64_t)x;
+  for (int j = 0; j < NP; ++j) {
+    const G* src = gt + (size_t)(r0 + j < rows ? r0 + j : r0) * N;
+#pragma unroll
+    for (int a = 0; a < 16; ++a) v[j][a] = lift_coef<PM>(*coef_ptr<LOGN, PM>(src, tid, a), P.q);
   }
-  ntt_fwd<LOGN>(v, lds, tid, tws.tw[l], P);
-  uint2* dst = dbres + (size_t)b * N;
+  ntt_fwd<LOGN, PM, NP>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    uint2 y;
-    split27(v[a], y.x, y.y);
-    dst[ntt_slot<LOGN>(tid, a)] = y;
+  for (int j = 0; j < NP; ++j) {
+    if (r0 + j >= rows) break;
+    uint64_t* dst = reinterpret_cast<uint64_t*>(dbres) + (((size_t)l * C + k0) * d + r0 + j) * N;
+#pragma unroll
+    for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[j][a]);
   }
 }
 
@@ -1252,7 +1316,7 @@ k_encode_ntt(const G* __restrict__ gt, uint2* __restrict__ dbres, int k0, int nk
 // --------------------------------------------------------------------------
 
 // Workgroup per limb: NTT of the ternary secret lifted mod q_l.
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T)
 k_sk_ntt(const int8_t* __restrict__ sk, uint64_t* __restrict__ out, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
@@ -1262,10 +1326,9 @@ k_sk_ntt(const int8_t* __restrict__ sk, uint64_t* __restrict__ out, PrimeSet ps,
   uint64_t v[16];
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
-    const int x = sk[coef_index<LOGN>(tid, a)];
-    v[a] = x < 0 ? P.q - (uint64_t)(-x) : (uint64_t)x;
+    v[a] = lift_coef<PM>(sk[coef_index<LOGN>(tid, a)], P.q);
   }
-  ntt_fwd<LOGN>(v, lds, tid, tws.tw[l], P);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
   for (int a = 0; a < 16; ++a) out[(size_t)l * N + ntt_slot<LOGN>(tid, a)] = v[a];
 }
@@ -1357,7 +1420,7 @@ k_sample_e(uint64_t seed, uint32_t purpose, int d, int N, long total, int16_t* _
 }
 
 // Workgroup per (query, coordinate, limb): c1 = a, c0 = -a s + e + Delta m.
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T)
 k_encrypt(const uint64_t* __restrict__ a_in, const int16_t* __restrict__ e_in,
           const int32_t* __restrict__ msgs, const uint64_t* __restrict__ sk_ntt,
@@ -1373,11 +1436,11 @@ k_encrypt(const uint64_t* __restrict__ a_in, const int16_t* __restrict__ e_in,
   uint64_t v[16];
 #pragma unroll
   for (int x = 0; x < 16; ++x) v[x] = a[coef_index<LOGN>(tid, x)];
-  ntt_fwd<LOGN>(v, lds, tid, tws.tw[l], P);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
   for (int x = 0; x < 16; ++x)
-    v[x] = mulmod(v[x], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, x)], P);
-  ntt_inv<LOGN>(v, lds, tid, tws.tw[l] + N, P);
+    v[x] = mulmod<PM>(v[x], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, x)], P);
+  ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
   // message [m]_t as a constant: Delta m in coefficient 0
   const int64_t mraw = msgs[qd];
   int64_t mm = mraw % (int64_t)t;
@@ -1476,7 +1539,7 @@ __device__ __forceinline__ uint32_t crt_round(const uint64_t* xl, int L, const P
 
 // Workgroup per ciphertext: x_l = INTT(NTT(c1) NTT(s)) + c0 per limb, then the
 // exact decode and the client share [m + ||q||^2]_t.
-template <int LOGN>
+template <int LOGN, bool PM>
 __global__ void __launch_bounds__(NttShape<LOGN>::T)
 k_decrypt(const uint64_t* __restrict__ ct, const uint64_t* __restrict__ sk_ntt,
           const uint32_t* __restrict__ qnorm2, uint32_t* __restrict__ outp, int L,
@@ -1492,11 +1555,11 @@ k_decrypt(const uint64_t* __restrict__ ct, const uint64_t* __restrict__ sk_ntt,
     uint64_t v[16];
 #pragma unroll
     for (int a = 0; a < 16; ++a) v[a] = c1[coef_index<LOGN>(tid, a)];
-    ntt_fwd<LOGN>(v, lds, tid, tws.tw[l], P);
+    ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
     for (int a = 0; a < 16; ++a)
-      v[a] = mulmod(v[a], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, a)], P);
-    ntt_inv<LOGN>(v, lds, tid, tws.tw[l] + N, P);
+      v[a] = mulmod<PM>(v[a], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, a)], P);
+    ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
 #pragma unroll
     for (int a = 0; a < 16; ++a) {
       const uint64_t r = addmod(v[a], c0[coef_index<LOGN>(tid, a)], P.q);
@@ -1570,31 +1633,60 @@ k_add_plain(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
 // instantiated for log2 N = 4 .. 14.
 #define SANNS_LOGN_CASES(X) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14)
 
+// The kernel's form for this context's primes (a context's twiddle tables are
+// built for the same choice).
+#define SANNS_PM(kern, ...) (ps.pm ? kern<__VA_ARGS__, true> : kern<__VA_ARGS__, false>)
+
 template <int LG, typename K, typename... A>
 static void ntt_launch(K kern, unsigned grid, hipStream_t st, A... args) {
   hipLaunchKernelGGL(kern, dim3(grid), dim3(NttShape<LG>::T), NttShape<LG>::lds_bytes, st,
                      args...);
 }
 
+// Whether a launch over n polynomials takes them in pairs: built for the PM
+// products at N >= 4096, and only with at least two pairs for each of the 256
+// CUs.  Below that the launch is a chain of latencies, not a stream, and more
+// workgroups of half the work end sooner (the forward transform of 512
+// polynomials of N = 4096: 21 us one by one, 25 us in pairs; of 24,576 of N =
+// 8192: 0.97 ms one by one, 0.78 ms in pairs).
+static bool ntt_pairs(const PrimeSet& ps, int logN, long n) {
+  return ps.pm && logN >= 12 && n >= 4 * 256;
+}
+
+// Launches the pair form where ntt_pairs says so, else the single form, of a
+// kernel template <.., NP, PM>; n polynomials, the grid rounded up to a
+// multiple of `align`; `items` in the arguments is the number of workgroups
+// that have work.
+#define SANNS_NTT_NP(LG, n, align, kern, targs, ...)                                         \
+  do {                                                                                       \
+    const bool pairs_ = ntt_pairs(ps, LG, (n));                                              \
+    const int items = (int)(pairs_ ? ((n) + 1) / 2 : (n));                                   \
+    const unsigned grid_ = (unsigned)((items + (align)-1) / (align) * (align));              \
+    if (pairs_) {                                                                            \
+      if constexpr (LG >= 12)                                                                \
+        hipLaunchKernelGGL((kern<SANNS_UNPACK targs, 2, true>), dim3(grid_),                 \
+                           dim3(NttShape<LG>::T), NttShape<LG>::lds_bytes_pair, st, __VA_ARGS__); \
+    } else {                                                                                 \
+      ntt_launch<LG>(SANNS_PM(kern, SANNS_UNPACK targs, 1), grid_, st, __VA_ARGS__);         \
+    }                                                                                        \
+  } while (0)
+#define SANNS_UNPACK(...) __VA_ARGS__
+
 hipError_t launch_ntt_fwd(const uint64_t* in, uint64_t* out, int n_polys, int logN, int L,
                           const PrimeSet& ps, const TwSet& tws, uint32_t* err, int split,
                           hipStream_t st, int d, int R) {
   if (n_polys <= 0) return hipSuccess;
+  if (n_polys % (2 * L)) return hipErrorInvalidValue;  // whole ciphertexts
   if (split == 2 && (logN < 5 || d <= 0 || n_polys != R * d * L)) return hipErrorInvalidValue;
-  bool pm = true;  // the matrix-core schedule's form: the short last reduction when it holds
-  for (int l = 0; l < L; ++l) pm = pm && pm_delta(ps.p[l].q) != 0;
   switch (logN) {
-#define SANNS_CASE(LG)                                                                    \
-  case LG:                                                                                \
-    if (split == 2 && pm)                                                                 \
-      ntt_launch<LG>(k_ntt_fwd<LG, 2, true>, (unsigned)n_polys, st, in, out, L, ps, tws, err, \
-                     d, R);                                                               \
-    else if (split == 2)                                                                  \
-      ntt_launch<LG>(k_ntt_fwd<LG, 2>, (unsigned)n_polys, st, in, out, L, ps, tws, err, d, R); \
-    else if (split == 1)                                                                  \
-      ntt_launch<LG>(k_ntt_fwd<LG, 1>, (unsigned)n_polys, st, in, out, L, ps, tws, err, d, R); \
-    else                                                                                  \
-      ntt_launch<LG>(k_ntt_fwd<LG, 0>, (unsigned)n_polys, st, in, out, L, ps, tws, err, d, R); \
+#define SANNS_CASE(LG)                                                                      \
+  case LG:                                                                                  \
+    if (split == 2)                                                                         \
+      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 2), in, out, L, ps, tws, err, d, R);     \
+    else if (split == 1)                                                                    \
+      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 1), in, out, L, ps, tws, err, d, R);     \
+    else                                                                                    \
+      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 0), in, out, L, ps, tws, err, d, R);     \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1610,7 +1702,7 @@ hipError_t launch_ntt_inv(uint64_t* io, int n_polys, int logN, int L, const Prim
   switch (logN) {
 #define SANNS_CASE(LG)                                                 \
   case LG:                                                             \
-    ntt_launch<LG>(k_ntt_inv<LG>, (unsigned)n_polys, st, io, L, ps, tws); \
+    ntt_launch<LG>(SANNS_PM(k_ntt_inv, LG), (unsigned)n_polys, st, io, L, ps, tws); \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1635,12 +1727,11 @@ hipError_t launch_intt_mask(uint64_t* ct, const uint32_t* share, const uint32_t*
                             const PrimeSet& ps, const TwSet& tws, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   const int n = M * 2 * L, Qa = work ? 0 : M / C;
-  const unsigned grid = (unsigned)((n + 7) / 8 * 8);
   switch (logN) {
 #define SANNS_CASE(LG)                                                                  \
   case LG:                                                                              \
-    ntt_launch<LG>(k_intt_mask<LG>, grid, st, ct, share, norms, work, C, L, t, ps, tws, \
-                   n, Qa);                                                              \
+    SANNS_NTT_NP(LG, n, 8, k_intt_mask, (LG), ct, share, norms, work, C, L, t, ps, tws, \
+                 items, Qa);                                                            \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1798,7 +1889,7 @@ static hipError_t launch_persistent_t(const PersistArgs& A, const PrimeSet& ps,
   constexpr int T = NttShape<LOGN>::T, S = T / (QG * CG);
   constexpr size_t lds_mac = MacDlShape<QT, CT, QG, CG, S, DI>::lds_bytes;
   constexpr size_t lds = lds_mac > NttShape<LOGN>::lds_bytes ? lds_mac : NttShape<LOGN>::lds_bytes;
-  auto kern = k_persistent<LOGN, QT, CT, QG, CG, DI, kPersistTileQ, kPersistTileC>;
+  auto kern = SANNS_PM(k_persistent, LOGN, QT, CT, QG, CG, DI, kPersistTileQ, kPersistTileC);
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1839,12 +1930,21 @@ template <typename G>
 static hipError_t launch_encode_ntt_t(const G* gt, uint2* dbres, int k0, int nk, int C, int d,
                                       int logN, int L, const PrimeSet& ps, const TwSet& tws,
                                       hipStream_t st) {
-  const unsigned grid = (unsigned)((long)L * nk * d);
-  if (grid == 0) return hipSuccess;
+  const long rows = (long)nk * d;
+  if (rows <= 0) return hipSuccess;
   switch (logN) {
 #define SANNS_CASE(LG)                                                                     \
   case LG:                                                                                 \
-    ntt_launch<LG>(k_encode_ntt<LG, G>, grid, st, gt, dbres, k0, nk, C, d, L, ps, tws);     \
+    if (ntt_pairs(ps, LG, L * rows)) {                                                     \
+      if constexpr (LG >= 12)                                                              \
+        hipLaunchKernelGGL((k_encode_ntt<LG, G, 2, true>),                                 \
+                           dim3((unsigned)(L * ((rows + 1) / 2))), dim3(NttShape<LG>::T),  \
+                           NttShape<LG>::lds_bytes_pair, st, gt, dbres, k0, nk, C, d, L,   \
+                           ps, tws);                                                       \
+    } else {                                                                               \
+      ntt_launch<LG>(SANNS_PM(k_encode_ntt, LG, G, 1), (unsigned)(L * rows), st, gt, dbres, \
+                     k0, nk, C, d, L, ps, tws);                                            \
+    }                                                                                      \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1908,7 +2008,7 @@ hipError_t launch_sk_ntt(const int8_t* sk, uint64_t* out, int logN, int L, const
   switch (logN) {
 #define SANNS_CASE(LG)                                                   \
   case LG:                                                               \
-    ntt_launch<LG>(k_sk_ntt<LG>, (unsigned)L, st, sk, out, ps, tws);     \
+    ntt_launch<LG>(SANNS_PM(k_sk_ntt, LG), (unsigned)L, st, sk, out, ps, tws);     \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1925,7 +2025,7 @@ hipError_t launch_rerand(const MaskKey& K, const uint64_t* qids, const uint32_t*
   switch (logN) {
 #define SANNS_CASE(LG)                                                                    \
   case LG:                                                                                \
-    ntt_launch<LG>(k_rerand<LG>, (unsigned)(M * L), st, K, qids, work, C, L, pk_ntt, ct, ps, \
+    ntt_launch<LG>(SANNS_PM(k_rerand, LG), (unsigned)(M * L), st, K, qids, work, C, L, pk_ntt, ct, ps, \
                    tws);                                                                  \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
@@ -1946,14 +2046,13 @@ hipError_t launch_intt_mask_cp(uint64_t* ct, const uint32_t* share, const uint32
   const long nf = (long)M * (N / 2);
   int8_t* errs = reinterpret_cast<int8_t*>(flood + (size_t)M * L * N);
   const int n = M * 2 * L, Qa = work ? 0 : M / C;
-  const unsigned grid = (unsigned)((n + 7) / 8 * 8);
   hipLaunchKernelGGL(k_cp_noise, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, st, K, qids,
                      work, C, (long)M, N, L, cp, ds, ps, flood, errs);
   switch (logN) {
-#define SANNS_CASE(LG)                                                                       \
-  case LG:                                                                                   \
-    ntt_launch<LG>(k_intt_mask_cp<LG>, grid, st, ct, share, norms, work, C, L, t,            \
-                   (const uint64_t*)flood, (const int8_t*)errs, ps, tws, n, Qa);              \
+#define SANNS_CASE(LG)                                                                     \
+  case LG:                                                                                 \
+    SANNS_NTT_NP(LG, n, 8, k_intt_mask_cp, (LG), ct, share, norms, work, C, L, t,          \
+                 (const uint64_t*)flood, (const int8_t*)errs, ps, tws, items, Qa);         \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1988,7 +2087,7 @@ hipError_t launch_encrypt(const uint64_t* a, const int16_t* e, const int32_t* ms
   switch (logN) {
 #define SANNS_CASE(LG)                                                                 \
   case LG:                                                                             \
-    ntt_launch<LG>(k_encrypt<LG>, (unsigned)(Qd * L), st, a, e, msgs, sk_ntt, ct, L, t, \
+    ntt_launch<LG>(SANNS_PM(k_encrypt, LG), (unsigned)(Qd * L), st, a, e, msgs, sk_ntt, ct, L, t, \
                    ps, tws);                                                           \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
@@ -2007,7 +2106,7 @@ hipError_t launch_decrypt(const uint64_t* ct, int M, const uint64_t* sk_ntt,
   switch (logN) {
 #define SANNS_CASE(LG)                                                                   \
   case LG:                                                                               \
-    ntt_launch<LG>(k_decrypt<LG>, (unsigned)M, st, ct, sk_ntt, qnorm2, out, L, ps, tws, D); \
+    ntt_launch<LG>(SANNS_PM(k_decrypt, LG), (unsigned)M, st, ct, sk_ntt, qnorm2, out, L, ps, tws, D); \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE

@@ -102,6 +102,81 @@ __device__ __forceinline__ uint64_t reduce_pm60(uint64_t x, uint32_t delta, uint
   return csub(r, q);
 }
 
+// --------------------------------------------------------------------------
+// products for primes q = 2^54 - delta, delta = pm_delta(q) != 0
+// --------------------------------------------------------------------------
+
+// A fixed operand w < q as the words (w mod 2^24, w >> 24) and the same two of
+// w' = w 2^32 mod q, in the 16 bytes of a (value, Shoup companion) pair.
+__host__ __device__ inline void pm_pair(uint64_t w, uint64_t w32, uint64_t* out) {
+  out[0] = (w & 0xffffffull) | ((w >> 24) << 32);
+  out[1] = (w32 & 0xffffffull) | ((w32 >> 24) << 32);
+}
+
+// Constants of the product, hidden from the optimiser so that 2^24 stays a
+// factor of a multiply-add.
+struct PmConst {
+  uint32_t c24;  // 2^24
+  int32_t d4;    // 4 delta
+};
+__device__ __forceinline__ PmConst pm_const(uint64_t q) {
+  PmConst c{1u << 24, (int32_t)(4 * pm_delta(q))};
+  asm("" : "+s"(c.c24));
+  return c;
+}
+
+// L + 2^24 H mod q, lazily: H = H1 2^32 + H0 and 2^56 = 4 delta (mod q) give
+// L + H0 2^24 + H1 4 delta.
+__device__ __forceinline__ uint64_t pm_join(uint64_t L, uint64_t H, const PmConst& c) {
+  const uint64_t r = L + (uint64_t)lo32(H) * c.c24;
+  return r + (uint64_t)((int64_t)(int32_t)hi32(H) * c.d4);
+}
+
+// x w (mod q) for a signed x, |x| < 2^62, as a signed value in
+// (-1.25 2^54, 10.4 2^54): with x = x1 2^32 + x0 (x1 signed), x w = x0 w + x1 w'
+// (mod q), both operands split at bit 24, so that the two sums
+//   L = x0 (w mod 2^24) + x1 (w' mod 2^24)    in (-2^54, 2^56 + 2^54)
+//   H = x0 (w >> 24)    + x1 (w' >> 24)       in (-2^60, 2^62 + 2^60)
+// never leave 64 bits and need no carries or masks: six multiply-adds, where
+// the estimated Shoup product takes eleven instructions.
+__device__ __forceinline__ uint64_t mul_pm(uint64_t x, u64x2 W, const PmConst& c) {
+  const uint32_t x0 = opaque(lo32(x));
+  const int32_t x1 = (int32_t)opaque(hi32(x));
+  const uint64_t L = mul32x32(x0, lo32(W.x)) + (uint64_t)((int64_t)x1 * (int32_t)lo32(W.y));
+  const uint64_t H = mul32x32(x0, hi32(W.x)) + (uint64_t)((int64_t)x1 * (int32_t)hi32(W.y));
+  return pm_join(L, H, c);
+}
+
+// x w (mod q) for x < 2^32, in [0, 2^57).
+__device__ __forceinline__ uint64_t mul_pm32(uint32_t x, uint64_t w, const PmConst& c) {
+  const uint64_t H = mul32x32(x, (uint32_t)(w >> 24));
+  const uint64_t r = mul32x32(x, (uint32_t)w & 0xffffffu) + (uint64_t)lo32(H) * c.c24;
+  return r + mul32x32(hi32(H), (uint32_t)c.d4);
+}
+
+// A signed value |x| < 2^62 reduced to [0, q): 512 q (just below 2^63) makes
+// it non-negative, then the fold by 2^54 = delta (below 2^54 + 2^32 < 2q).
+__device__ __forceinline__ uint64_t reduce_pm_signed(uint64_t x, uint32_t delta, uint64_t q) {
+  x += q << 9;
+  const uint64_t r = (uint64_t)(uint32_t)(x >> 54) * delta + (x & ((1ull << 54) - 1));
+  return csub(r, q);
+}
+
+// a b (mod q) in [0, 2^56) for a, b < 2^54: a b = p0 + m 2^32 + p2 2^64 in
+// 32-bit halves, folded twice by 2^54 = delta (first the 55 bits above 2^54,
+// then the 22 bits that their product with delta has above 2^54).
+__device__ __forceinline__ uint64_t mulmod_pm(uint64_t a, uint64_t b, uint32_t delta) {
+  const uint32_t a0 = opaque(lo32(a)), a1 = opaque(hi32(a)), b0 = lo32(b), b1 = hi32(b);
+  const uint64_t p0 = mul32x32(a0, b0);
+  const uint64_t m = mul32x32(a0, b1) + mul32x32(a1, b0) + hi32(p0);  // < 2^55 + 2^32
+  const uint64_t w = (m >> 22) + (mul32x32(a1, b1) << 10);            // < 2^55
+  const uint64_t z0 = mul32x32(lo32(w), delta);
+  const uint64_t z1 = mul32x32(hi32(w), delta) + hi32(z0);            // < 2^46
+  const uint64_t lo = (uint64_t)lo32(p0) + lo32(z0);
+  const uint32_t hi = (lo32(m) & 0x3fffffu) + (lo32(z1) & 0x3fffffu);
+  return lo + ((uint64_t)hi << 32) + mul32x32((uint32_t)(z1 >> 22), delta);
+}
+
 __device__ __forceinline__ uint64_t addmod(uint64_t a, uint64_t b, uint64_t q) {
   return csub(a + b, q);
 }
@@ -146,6 +221,13 @@ __device__ __forceinline__ uint64_t acc3_reduce(const Acc3 &a, const Prime &P) {
 __device__ __forceinline__ void split27(uint64_t x, uint32_t &x0, uint32_t &x1) {
   x0 = lo32(x) & ((1u << 27) - 1);
   x1 = (uint32_t)(x >> 27);
+}
+
+// The two halves as one word (low half in the low 32 bits).
+__device__ __forceinline__ uint64_t halves27(uint64_t x) {
+  uint32_t x0, x1;
+  split27(x, x0, x1);
+  return (uint64_t)x1 << 32 | x0;
 }
 
 }  // namespace sanns

@@ -12,12 +12,20 @@
 // output), followed by the factor psi^-j N^-1 per coefficient: the butterfly
 // at stride 2^p uses W_inv[2^p + (j mod 2^p)] = omega^-((j mod 2^p) N / 2^(p+1))
 // (stage 0 multiplies by 1).
-// Lazy reduction with the estimated Shoup quotient (products in [0, 4q) for
-// any input below 2^63): no reduction inside either transform -- each
-// butterfly maps values below B q to values below (B + 4) q (X + T and
-// X + 4q - T; the inverse's twiddle-free stage 0 maps inputs below q to
-// values below 3q), so after log2 N <= 14 stages they stay below 58 q < 2^60
-// -- and one reduction at the end.
+// No reduction inside either transform and one at the end, in two forms:
+//   PM (every prime of the context is 2^54 - delta, delta < 2^22: the primes
+//   that the library derives): signed values, products by mul_pm (six
+//   multiply-adds, |T| < 10.4 2^54 for |x| < 2^62), butterflies X + T and
+//   X - T.  A stage adds at most 10.4 2^54, so after log2 N <= 14 stages
+//   values stay within 147 2^54 < 2^62.  Nine VALU instructions per butterfly
+//   against 17 for the general form: what bounds a transform is then its
+//   memory traffic and not its arithmetic.
+//   general: unsigned values, estimated Shoup quotients (products in [0, 4q)
+//   for any input below 2^63), butterflies X + T and X + 4q - T (the inverse's
+//   twiddle-free stage 0 maps inputs below q to values below 3q), below 58 q
+//   < 2^60 after 14 stages.
+// The twiddle tables hold (w, Shoup companion) pairs, or for PM the words of
+// pm_pair.
 //
 // Stages are grouped in passes of up to four index bits; the narrow pass (if
 // log2 N is not a multiple of four) is the forward's first and the inverse's
@@ -52,6 +60,10 @@ struct NttShape {
   static constexpr int inv_b(int j) { return j == P - 1 ? R : 4; }
   // exchanges go through LDS in two 32-bit halves
   static constexpr size_t lds_bytes = (size_t)(N + (N >> 4)) * sizeof(uint32_t);
+  // a pair of polynomials: whole words, one polynomial after the other (in
+  // halves at N = 16384, where the words would leave no room on a CU)
+  static constexpr bool pair_words = LOGN < 14;
+  static constexpr size_t lds_bytes_pair = lds_bytes * (pair_words ? 2 : 1);
 };
 
 __device__ __forceinline__ constexpr int lds_pad(int idx) { return idx + (idx >> 4); }
@@ -78,37 +90,122 @@ __device__ __forceinline__ int ntt_slot(int tid, int a) {
   return a * NttShape<LOGN>::T + tid;
 }
 
+// Slot a's entry of a vector in coefficient or NTT form, `base` uniform: a
+// uniform address (kept as one by an empty asm statement) plus the thread's
+// 32-bit offset, so that 16 words cost no per-thread addresses.  (Left alone,
+// the compiler forms one 64-bit address per thread and word and keeps them
+// from the loads to the stores, 64 registers for a pair of polynomials.)  UNI:
+// the PM forms of whole wavefronts; the compiler does not take it in some of
+// the general ones.
+template <typename V>
+using GlobalPtr = __attribute__((address_space(1))) V*;
+template <int LOGN, bool UNI, typename V>
+__device__ __forceinline__ GlobalPtr<V> uniform_ptr(V* p) {
+  GlobalPtr<V> g = (GlobalPtr<V>)p;
+  if constexpr (UNI && LOGN >= 10) asm("" : "+s"(g));
+  return g;
+}
+template <int LOGN, bool UNI, typename V>
+__device__ __forceinline__ GlobalPtr<V> coef_ptr(V* base, int tid, int a) {
+  return uniform_ptr<LOGN, UNI>(base + coef_index<LOGN>(0, a)) + (unsigned)coef_index<LOGN>(tid, 0);
+}
+template <int LOGN, bool UNI, typename V>
+__device__ __forceinline__ GlobalPtr<V> ntt_ptr(V* base, int tid, int a) {
+  return uniform_ptr<LOGN, UNI>(base + ntt_slot<LOGN>(0, a)) + (unsigned)tid;
+}
+
+typedef uint64_t Vec2 __attribute__((ext_vector_type(2)));
+
+// A run of twiddles.  UNIFORM: the base is the same across the wavefront, and
+// the loads are scalar (constant address space: the compiler does not take a
+// load after a barrier for invariant by itself).
+template <bool UNIFORM>
+struct TwPtr {
+  const u64x2* p;
+  __device__ __forceinline__ TwPtr(const u64x2* tw, int b) : p(tw + b) {}
+  __device__ __forceinline__ u64x2 operator[](int i) const { return p[i]; }
+};
+template <>
+struct TwPtr<true> {
+  typedef const __attribute__((address_space(4))) Vec2* C;
+  C p;
+  __device__ __forceinline__ TwPtr(const u64x2* tw, int b)
+      : p((C)(tw + __builtin_amdgcn_readfirstlane(b))) {}
+  __device__ __forceinline__ u64x2 operator[](int i) const {
+    const Vec2 v = p[i];
+    return u64x2(v.x, v.y);
+  }
+};
+
 // Twiddles of one stage (p1 = p + 1): (N + eidx(tid, a0)) >> p1 is
 // ((N + eidx(tid, 0)) >> p1) + (eidx(0, a0) >> p1).  When every lane bit of
 // the thread id sits below bit LO the base is the same across the wavefront.
+// In the last pass (LO = 0) a thread's 8 >> p twiddles of stage p are
+// neighbours in that order, a stride of up to 128 bytes between lanes; the
+// table holds those stages transposed, twiddle g of thread tid at (N >> p1) +
+// g T + tid, so that a wavefront's load covers whole lines.
 template <int LOGN, int B, int LO>
-__device__ __forceinline__ const u64x2* tw_stage(const u64x2* tw, int tid, int p1) {
-  int b = (NttShape<LOGN>::N + eidx<LOGN, B, LO>(tid, 0)) >> p1;
-  if (LO >= 6) b = __builtin_amdgcn_readfirstlane(b);
-  return tw + b;
+__device__ __forceinline__ TwPtr<(LO >= 6)> tw_stage(const u64x2* tw, int tid, int p1) {
+  if constexpr (LO == 0) return TwPtr<false>(tw, (NttShape<LOGN>::N >> p1) + tid);
+  else return TwPtr<(LO >= 6)>(tw, (NttShape<LOGN>::N + eidx<LOGN, B, LO>(tid, 0)) >> p1);
+}
+template <int LOGN, int B, int LO>
+__device__ __forceinline__ constexpr int tw_index(int a0, int p1) {
+  return LO == 0 ? (a0 >> p1) * NttShape<LOGN>::T : eidx<LOGN, B, LO>(0, a0) >> p1;
 }
 
-template <int LOGN, int B, int LO>
-__device__ __forceinline__ void fwd_pass(uint64_t (&v)[16], int tid,
-                                         const u64x2* __restrict__ tw, uint64_t q) {
-  const uint64_t q4 = 4 * q, nq = 0 - q;
+// Butterfly arithmetic of the two forms (see the top of the file).
+template <bool PM>
+struct Arith;
+template <>
+struct Arith<false> {
+  uint64_t q4, q2, nq;
+  __device__ __forceinline__ explicit Arith(uint64_t q) : q4(4 * q), q2(2 * q), nq(0 - q) {}
+  __device__ __forceinline__ uint64_t mul(uint64_t x, u64x2 W) const {
+    return shoup_approx(x, W.x, W.y, nq);
+  }
+  __device__ __forceinline__ uint64_t sub(uint64_t x, uint64_t t) const { return (x + q4) - t; }
+  __device__ __forceinline__ uint64_t sub0(uint64_t x, uint64_t y) const { return (x + q2) - y; }
+};
+template <>
+struct Arith<true> {
+  PmConst c;
+  __device__ __forceinline__ explicit Arith(uint64_t q) : c(pm_const(q)) {}
+  __device__ __forceinline__ uint64_t mul(uint64_t x, u64x2 W) const { return mul_pm(x, W, c); }
+  __device__ __forceinline__ uint64_t sub(uint64_t x, uint64_t t) const { return x - t; }
+  __device__ __forceinline__ uint64_t sub0(uint64_t x, uint64_t y) const { return x - y; }
+};
+
+// A small signed coefficient (|x| < 2^31) as a transform input.
+template <bool PM>
+__device__ __forceinline__ uint64_t lift_coef(int64_t x, uint64_t q) {
+  return PM || x >= 0 ? (uint64_t)x : q - (uint64_t)(-x);
+}
+
+// NP polynomials of one limb share each twiddle.
+template <int LOGN, int B, int LO, bool PM, int NP>
+__device__ __forceinline__ void fwd_pass(uint64_t (&v)[NP][16], int tid,
+                                         const u64x2* __restrict__ tw, const Arith<PM>& A) {
 #pragma unroll
   for (int rp = B - 1; rp >= 0; --rp) {
     const int p = LO + rp;
-    const u64x2* tb = tw_stage<LOGN, B, LO>(tw, tid, p + 1);
+    const auto tb = tw_stage<LOGN, B, LO>(tw, tid, p + 1);
 #pragma unroll
     for (int e = 0; e < (16 >> B); ++e) {
 #pragma unroll
       for (int g = 0; g < (1 << (B - 1 - rp)); ++g) {
         const int a0 = (e << B) | (g << (rp + 1));
-        const u64x2 W = tb[eidx<LOGN, B, LO>(0, a0) >> (p + 1)];
+        const u64x2 W = tb[tw_index<LOGN, B, LO>(a0, p + 1)];
 #pragma unroll
         for (int l = 0; l < (1 << rp); ++l) {
           const int a = a0 | l, b = a | (1 << rp);
-          const uint64_t X = v[a];
-          const uint64_t Tm = shoup_approx(v[b], W.x, W.y, nq);
-          v[a] = X + Tm;
-          v[b] = (X + q4) - Tm;
+#pragma unroll
+          for (int j = 0; j < NP; ++j) {
+            const uint64_t X = v[j][a];
+            const uint64_t Tm = A.mul(v[j][b], W);
+            v[j][a] = X + Tm;
+            v[j][b] = A.sub(X, Tm);
+          }
         }
       }
     }
@@ -119,20 +216,17 @@ __device__ __forceinline__ void fwd_pass(uint64_t (&v)[16], int tid,
 // is (2^p + (eidx(tid, 0) mod 2^p)) + (eidx(0, x) mod 2^p).  Only in the pass
 // over the lowest bits does j mod 2^p not involve the thread id.
 template <int LOGN, int B, int LO>
-__device__ __forceinline__ const u64x2* tw_inv_stage(const u64x2* tw, int tid, int p) {
-  int b = (1 << p) + (eidx<LOGN, B, LO>(tid, 0) & ((1 << p) - 1));
-  if (LO == 0) b = __builtin_amdgcn_readfirstlane(b);
-  return tw + b;
+__device__ __forceinline__ TwPtr<(LO == 0)> tw_inv_stage(const u64x2* tw, int tid, int p) {
+  return TwPtr<(LO == 0)>(tw, (1 << p) + (eidx<LOGN, B, LO>(tid, 0) & ((1 << p) - 1)));
 }
 
-template <int LOGN, int B, int LO>
-__device__ __forceinline__ void inv_pass(uint64_t (&v)[16], int tid,
-                                         const u64x2* __restrict__ tw, uint64_t q) {
-  const uint64_t q2 = 2 * q, q4 = 4 * q, nq = 0 - q;
+template <int LOGN, int B, int LO, bool PM, int NP>
+__device__ __forceinline__ void inv_pass(uint64_t (&v)[NP][16], int tid,
+                                         const u64x2* __restrict__ tw, const Arith<PM>& A) {
 #pragma unroll
   for (int rp = 0; rp < B; ++rp) {
     const int p = LO + rp;
-    const u64x2* tb = tw_inv_stage<LOGN, B, LO>(tw, tid, p);
+    const auto tb = tw_inv_stage<LOGN, B, LO>(tw, tid, p);
 #pragma unroll
     for (int e = 0; e < (16 >> B); ++e) {
 #pragma unroll
@@ -141,16 +235,20 @@ __device__ __forceinline__ void inv_pass(uint64_t (&v)[16], int tid,
 #pragma unroll
         for (int l = 0; l < (1 << rp); ++l) {
           const int a = a0 | l, b = a | (1 << rp);
-          const uint64_t X = v[a], Y = v[b];
-          if (p == 0) {
-            // twiddle 1; inputs are below q
-            v[a] = X + Y;
-            v[b] = (X + q2) - Y;
-          } else {
-            const u64x2 W = tb[eidx<LOGN, B, LO>(0, a) & ((1 << p) - 1)];
-            const uint64_t Tm = shoup_approx(Y, W.x, W.y, nq);
-            v[a] = X + Tm;
-            v[b] = (X + q4) - Tm;
+          u64x2 W;
+          if (p > 0) W = tb[eidx<LOGN, B, LO>(0, a) & ((1 << p) - 1)];
+#pragma unroll
+          for (int j = 0; j < NP; ++j) {
+            const uint64_t X = v[j][a], Y = v[j][b];
+            if (p == 0) {
+              // twiddle 1; inputs are below q
+              v[j][a] = X + Y;
+              v[j][b] = A.sub0(X, Y);
+            } else {
+              const uint64_t Tm = A.mul(Y, W);
+              v[j][a] = X + Tm;
+              v[j][b] = A.sub(X, Tm);
+            }
           }
         }
       }
@@ -186,69 +284,124 @@ __device__ __forceinline__ void lds_exchange(uint64_t (&v)[16], uint64_t* lds, i
     v[a] = lo[a] | ((uint64_t)ld[lds_pad(eidx<LOGN, B1, LO1>(0, a))] << 32);
 }
 
-template <int LOGN, int J>
-__device__ __forceinline__ void fwd_from(uint64_t (&v)[16], uint64_t* lds, int tid,
-                                         const u64x2* __restrict__ tw, uint64_t q) {
+// The same for a pair of polynomials, in whole 64-bit words through a buffer
+// of one polynomial: three barriers for both.
+template <int LOGN, int B0, int LO0, int B1, int LO1>
+__device__ __forceinline__ void lds_exchange_pair(uint64_t (&v)[2][16], uint64_t* lds, int tid) {
+  uint64_t* st = lds + lds_pad(eidx<LOGN, B0, LO0>(tid, 0));
+  const uint64_t* ld = lds + lds_pad(eidx<LOGN, B1, LO1>(tid, 0));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (j) __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 16; ++a) st[lds_pad(eidx<LOGN, B0, LO0>(0, a))] = v[j][a];
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 16; ++a) v[j][a] = ld[lds_pad(eidx<LOGN, B1, LO1>(0, a))];
+  }
+}
+
+template <int LOGN, int B0, int LO0, int B1, int LO1, int NP>
+__device__ __forceinline__ void exchange(uint64_t (&v)[NP][16], uint64_t* lds, int tid) {
+  if constexpr (NP == 2 && NttShape<LOGN>::pair_words) {
+    lds_exchange_pair<LOGN, B0, LO0, B1, LO1>(v, lds, tid);
+  } else {
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      if (j) __syncthreads();
+      lds_exchange<LOGN, B0, LO0, B1, LO1>(v[j], lds, tid);
+    }
+  }
+}
+
+template <int LOGN, int J, bool PM, int NP>
+__device__ __forceinline__ void fwd_from(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
+                                         const u64x2* __restrict__ tw, const Arith<PM>& A) {
   using S = NttShape<LOGN>;
   constexpr int LO = S::fwd_lo(J), B = S::fwd_b(J);
-  fwd_pass<LOGN, B, LO>(v, tid, tw, q);
+  fwd_pass<LOGN, B, LO, PM, NP>(v, tid, tw, A);
   if constexpr (J + 1 < S::P) {
     // the barrier before the first store guards LDS still read by an
     // earlier transform of the workgroup
     if (J == 0) __syncthreads();
-    lds_exchange<LOGN, B, LO, S::fwd_b(J + 1), S::fwd_lo(J + 1)>(v, lds, tid);
-    fwd_from<LOGN, J + 1>(v, lds, tid, tw, q);
+    exchange<LOGN, B, LO, S::fwd_b(J + 1), S::fwd_lo(J + 1), NP>(v, lds, tid);
+    fwd_from<LOGN, J + 1, PM, NP>(v, lds, tid, tw, A);
   }
 }
 
-template <int LOGN, int J>
-__device__ __forceinline__ void inv_from(uint64_t (&v)[16], uint64_t* lds, int tid,
-                                         const u64x2* __restrict__ tw, const Prime& P) {
+template <int LOGN, int J, bool PM, int NP>
+__device__ __forceinline__ void inv_from(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
+                                         const u64x2* __restrict__ tw, const Arith<PM>& A) {
   using S = NttShape<LOGN>;
   constexpr int LO = S::inv_lo(J), B = S::inv_b(J);
-  inv_pass<LOGN, B, LO>(v, tid, tw, P.q);
+  inv_pass<LOGN, B, LO, PM, NP>(v, tid, tw, A);
   if constexpr (J + 1 < S::P) {
     if (J == 0) __syncthreads();
-    lds_exchange<LOGN, B, LO, S::inv_b(J + 1), S::inv_lo(J + 1)>(v, lds, tid);
-    inv_from<LOGN, J + 1>(v, lds, tid, tw, P);
+    exchange<LOGN, B, LO, S::inv_b(J + 1), S::inv_lo(J + 1), NP>(v, lds, tid);
+    inv_from<LOGN, J + 1, PM, NP>(v, lds, tid, tw, A);
   }
 }
 
-// Forward transform.  Input: residues below q, slot a = coefficient
-// coef_index(tid, a).  Output: slot a = evaluation a + 16 tid in [0, q).
-// lds holds NttShape<LOGN>::lds_bytes; the caller synchronises before reusing it.
-// PM: q = 2^54 - delta with delta = pm_delta(q) != 0 (the last reduction by
-// 2^54 = delta (mod q) instead of a Shoup product).
-template <int LOGN, bool PM = false>
-__device__ __forceinline__ void ntt_fwd(uint64_t (&v)[16], uint64_t* lds, int tid,
+// Forward transform of NP polynomials of one limb.  Input: residues below q
+// (PM: signed, |x| < 2^54), slot a = coefficient coef_index(tid, a).  Output:
+// slot a = evaluation a + 16 tid in [0, q).  lds holds NttShape<LOGN>::lds_bytes
+// (lds_bytes_pair for NP = 2); the caller synchronises before reusing it.
+template <int LOGN, bool PM, int NP>
+__device__ __forceinline__ void ntt_fwd(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
                                         const u64x2* __restrict__ tw, const Prime& P) {
-  static_assert(LOGN <= 14, "forward values must stay below 2^60");
-  fwd_from<LOGN, 0>(v, lds, tid, tw, P.q);
+  static_assert(LOGN <= 14, "forward values must stay within their bounds");
+  fwd_from<LOGN, 0, PM, NP>(v, lds, tid, tw, Arith<PM>(P.q));
   const uint64_t nq = 0 - P.q;
   const uint32_t pd = pm_delta(P.q);
 #pragma unroll
-  for (int a = 0; a < 16; ++a)
-    v[a] = PM ? reduce_pm60(v[a], pd, P.q)
-              : csub(csub(shoup_approx(v[a], 1, P.one, nq), 2 * P.q), P.q);
+  for (int j = 0; j < NP; ++j)
+#pragma unroll
+    for (int a = 0; a < 16; ++a)
+      v[j][a] = PM ? reduce_pm_signed(v[j][a], pd, P.q)
+                   : csub(csub(shoup_approx(v[j][a], 1, P.one, nq), 2 * P.q), P.q);
+}
+
+template <int LOGN, bool PM>
+__device__ __forceinline__ void ntt_fwd(uint64_t (&v)[16], uint64_t* lds, int tid,
+                                        const u64x2* __restrict__ tw, const Prime& P) {
+  ntt_fwd<LOGN, PM, 1>(reinterpret_cast<uint64_t(&)[1][16]>(v), lds, tid, tw, P);
 }
 
 // Inverse transform.  Input: residues below q, slot a = evaluation a + 16 tid
 // (the forward's output order).  Output: slot a = coefficient
-// coef_index(tid, a) in [0, q).  tw points at the limb's inverse stage table,
-// which is followed by the N (psi^-j N^-1, companion) pairs of the final
-// factor.
-template <int LOGN>
-__device__ __forceinline__ void ntt_inv(uint64_t (&v)[16], uint64_t* lds, int tid,
+// coef_index(tid, a) in [0, q), or with PM and LAZY a signed value in (-1.25
+// 2^54, 10.4 2^54), for callers that add terms before the reduction.  tw
+// points at the limb's inverse stage table, which is followed by the N pairs
+// of the final factor psi^-j N^-1.
+template <int LOGN, bool PM, bool LAZY, int NP>
+__device__ __forceinline__ void ntt_inv(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
                                         const u64x2* __restrict__ tw, const Prime& P) {
-  static_assert(LOGN <= 14, "inverse values must stay below 2^60");
-  inv_from<LOGN, 0>(v, lds, tid, tw, P);
-  const u64x2* F = tw + NttShape<LOGN>::N;
-  const uint64_t nq = 0 - P.q;
+  static_assert(LOGN <= 14, "inverse values must stay within their bounds");
+  const Arith<PM> A(P.q);
+  inv_from<LOGN, 0, PM, NP>(v, lds, tid, tw, A);
+  const Vec2* F = reinterpret_cast<const Vec2*>(tw + NttShape<LOGN>::N);
+  const uint32_t pd = pm_delta(P.q);
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
-    const u64x2 f = F[coef_index<LOGN>(tid, a)];
-    v[a] = csub(csub(shoup_approx(v[a], f.x, f.y, nq), 2 * P.q), P.q);
+    const Vec2 fv = *coef_ptr<LOGN, PM>(F, tid, a);
+    const u64x2 f(fv.x, fv.y);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const uint64_t r = A.mul(v[j][a], f);
+      if constexpr (PM)
+        v[j][a] = LAZY ? r : reduce_pm60(r + 2 * P.q, pd, P.q);
+      else
+        v[j][a] = csub(csub(r, 2 * P.q), P.q);
+    }
+    // at most four factors (16 registers) in flight
+    if (NP > 1 && a % 4 == 3) __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+template <int LOGN, bool PM, bool LAZY = false>
+__device__ __forceinline__ void ntt_inv(uint64_t (&v)[16], uint64_t* lds, int tid,
+                                        const u64x2* __restrict__ tw, const Prime& P) {
+  ntt_inv<LOGN, PM, LAZY, 1>(reinterpret_cast<uint64_t(&)[1][16]>(v), lds, tid, tw, P);
 }
 
 }  // namespace sanns

@@ -100,7 +100,7 @@ static uint32_t bitrev(uint32_t x, int bits) {
   return r;
 }
 
-std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi) {
+std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi, bool pm) {
   int logN = 0;
   while ((1u << logN) < N) ++logN;
   const uint64_t ipsi = powmod(psi, q - 2, q);
@@ -112,26 +112,38 @@ std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi) {
     pw[i] = mulmod(pw[i - 1], psi, q);
     iww[i] = mulmod(iww[i - 1], iw, q);
   }
-  // [0, 2N): forward (Psi_rev, companion) pairs;
+  // pairs (w, Shoup companion), or the words of pm_pair:
+  // [0, 2N): forward Psi_rev pairs;
   // [2N, 4N): inverse stage pairs, entry 2^p + m = omega^-(m N / 2^(p+1));
   // [4N, 6N): final factor psi^-j N^-1 pairs in coefficient order.
   std::vector<uint64_t> t(6 * (size_t)N, 0);
-  for (uint32_t m = 0; m < N; ++m) {
-    const uint32_t r = bitrev(m, logN);
-    t[2 * (size_t)m] = pw[r];
-    t[2 * (size_t)m + 1] = shoup_companion(pw[r], q);
-  }
-  for (int p = 0; p < logN; ++p)
-    for (uint32_t m = 0; m < (1u << p); ++m) {
-      const uint64_t w = iww[(size_t)m * (N >> (p + 1))];
-      const size_t i = 2 * (size_t)N + 2 * ((1u << p) + m);
+  auto put = [&](size_t i, uint64_t w) {
+    if (pm) {
+      pm_pair(w, (uint64_t)(((u128)w << 32) % q), &t[i]);
+    } else {
       t[i] = w;
       t[i + 1] = shoup_companion(w, q);
     }
+  };
+  for (uint32_t m = 0; m < N; ++m) {
+    // the last pass's stages (m >= N / 16, 8 >> p twiddles of each of the
+    // N / 16 threads) are stored transposed, [8 >> p][N / 16]
+    uint32_t at = m;
+    if (m >= N / 16 && m) {
+      uint32_t base = N / 16;
+      while (2 * base <= m) base *= 2;
+      const uint32_t per = base / (N / 16), tid = (m - base) / per, g = (m - base) % per;
+      at = base + g * (N / 16) + tid;
+    }
+    put(2 * (size_t)at, pw[bitrev(m, logN)]);
+  }
+  for (int p = 0; p < logN; ++p)
+    for (uint32_t m = 0; m < (1u << p); ++m) {
+      put(2 * (size_t)N + 2 * ((1u << p) + m), iww[(size_t)m * (N >> (p + 1))]);
+    }
   uint64_t f = ninv;
   for (uint32_t j = 0; j < N; ++j) {
-    t[4 * (size_t)N + 2 * j] = f;
-    t[4 * (size_t)N + 2 * j + 1] = shoup_companion(f, q);
+    put(4 * (size_t)N + 2 * j, f);
     f = mulmod(f, ipsi, q);
   }
   return t;

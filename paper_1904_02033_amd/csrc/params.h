@@ -21,8 +21,9 @@ uint64_t plain_modulus(uint32_t N, uint32_t bits);
 // Smallest primitive 2N-th root of unity mod q.
 uint64_t min_primitive_root_2n(uint32_t N, uint64_t q);
 
-// Twiddles of one prime: [4][N] = psi_rev, psi_rev', ipsi_rev, ipsi_rev'.
-std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi);
+// Twiddles of one prime (N forward, N inverse stage and N final factor pairs):
+// (w, Shoup companion) pairs, or with pm the words of pm_pair.
+std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi, bool pm);
 
 Prime prime_consts(uint32_t N, uint64_t q, uint64_t delta_mod_q);
 DigitConst digit_consts(uint64_t q);

@@ -393,11 +393,13 @@ extern "C" sanns_status sanns_ctx_create(const sanns_params* p, int device, sann
   const auto deltas = host::delta_mod_limbs(qs, p->t);
   std::vector<uint64_t> tw_all;
   try {
+    ctx->ps.pm = 1;
+    for (uint32_t l = 0; l < L; ++l) ctx->ps.pm &= pm_delta(qs[l]) != 0;
     for (uint32_t l = 0; l < L; ++l) {
       ctx->ps.p[l] = host::prime_consts(N, qs[l], deltas[l]);
       ctx->ds.c[l] = host::digit_consts(qs[l]);
       const uint64_t psi = host::min_primitive_root_2n(N, qs[l]);
-      const auto tw = host::twiddle_table(N, qs[l], psi);
+      const auto tw = host::twiddle_table(N, qs[l], psi, ctx->ps.pm != 0);
       tw_all.insert(tw_all.end(), tw.begin(), tw.end());
     }
     ctx->dec = host::decode_consts(qs, p->t);

@@ -126,6 +126,84 @@ def test_short_horner_step():
             assert reduce_short(y, q) == (r * (1 << 32) + w) % q, (q, r, w)
 
 
+def _pm_join(L, H, q):
+    """L + 2^24 H (mod q) as the device forms it: every factor and sum within
+    its 32- or 64-bit type."""
+    delta = (1 << 54) - q
+    assert -(1 << 63) <= L < 1 << 63 and -(1 << 63) <= H < 1 << 63
+    h0, h1 = H & 0xFFFFFFFF, H >> 32
+    assert -(1 << 31) <= h1 < 1 << 31 and 4 * delta < 1 << 31
+    r = L + h0 * (1 << 24)
+    assert -(1 << 63) <= r < 1 << 63
+    r += h1 * 4 * delta
+    assert -(1 << 63) <= r < 1 << 63
+    return r
+
+
+def mul_pm(x, w, q):
+    """The transforms' product of a signed x, |x| < 2^62, by a fixed w < q."""
+    wp = (w << 32) % q
+    x0, x1 = x & 0xFFFFFFFF, x >> 32
+    assert -(1 << 31) <= x1 < 1 << 31
+    words = [w & 0xFFFFFF, w >> 24, wp & 0xFFFFFF, wp >> 24]
+    assert all(0 <= v < 1 << 30 for v in words)
+    return _pm_join(x0 * words[0] + x1 * words[2], x0 * words[1] + x1 * words[3], q)
+
+
+def reduce_signed(x, q):
+    delta = (1 << 54) - q
+    x += q << 9
+    assert 0 <= x < 1 << 64
+    r = (x >> 54) * delta + (x & ((1 << 54) - 1))
+    assert r < 2 * q
+    return r - q if r >= q else r
+
+
+def mulmod_pm(a, b, q):
+    """Product of two residues, folded twice; every 32-bit factor checked."""
+    delta = (1 << 54) - q
+    a0, a1, b0, b1 = a & 0xFFFFFFFF, a >> 32, b & 0xFFFFFFFF, b >> 32
+    p0 = a0 * b0
+    m = a0 * b1 + a1 * b0 + (p0 >> 32)
+    w = (m >> 22) + ((a1 * b1) << 10)
+    assert m < 1 << 64 and w < 1 << 64
+    z0 = (w & 0xFFFFFFFF) * delta
+    z1 = (w >> 32) * delta + (z0 >> 32)
+    assert (z1 >> 22) < 1 << 32
+    lo = (p0 & 0xFFFFFFFF) + (z0 & 0xFFFFFFFF)
+    hi = (m & 0x3FFFFF) + (z1 & 0x3FFFFF)
+    return lo + (hi << 32) + (z1 >> 22) * delta
+
+
+def test_transform_products():
+    """mul_pm over |x| < 2^62 (a butterfly's T, which a stage adds to or
+    subtracts from a value: 14 stages stay within 147 2^54 < 2^62), mul_pm32,
+    mulmod_pm and the transforms' last reduction."""
+    unit = 1 << 54
+    lo, hi = -5 * unit // 4, 52 * unit // 5
+    assert unit + 14 * hi < 1 << 62 and hi + (1 << 57) + (1 << 55) < 1 << 60
+    for q in _short_primes():
+        rng = random.Random(q + 3)
+        xs = [0, 1, -1, (1 << 62) - 1, -(1 << 62) + 1, (1 << 32) - 1, 1 << 32, -(1 << 32),
+              ((1 << 30) - 1) << 32, -((1 << 30) << 32) + 0xFFFFFFFF]
+        ws = [0, 1, q - 1, (1 << 24) - 1, q >> 1, q - (1 << 24)]
+        xs += [rng.randrange(-(1 << 62) + 1, 1 << 62) for _ in range(300)]
+        ws += [rng.randrange(q) for _ in range(30)]
+        for w in ws:
+            for x in xs:
+                r = mul_pm(x, w, q)
+                assert lo < r < hi and r % q == x * w % q, (q, x, w)
+                assert reduce_signed(x, q) == x % q
+            for x in [0, (1 << 31) - 1] + [rng.randrange(1 << 31) for _ in range(20)]:
+                H = x * (w >> 24)
+                r = x * (w & 0xFFFFFF) + (H & 0xFFFFFFFF) * (1 << 24) + (H >> 32) * 4 * (unit - q)
+                assert 0 <= r < 1 << 57 and r % q == x * w % q
+        for a in [0, 1, q - 1, (1 << 32) - 1, 1 << 32] + [rng.randrange(q) for _ in range(100)]:
+            for b in [0, 1, q - 1, (1 << 32) - 1, 1 << 53] + [rng.randrange(q) for _ in range(20)]:
+                r = mulmod_pm(a, b, q)
+                assert 0 <= r < 1 << 56 and r % q == a * b % q
+
+
 def test_workload_primes_take_the_short_forms():
     """The primes of every workload here (N = 4096 ... 16384, L <= 3) are
     2^54 - delta with delta < 2^22, so the batched schedules run the short
