@@ -1350,13 +1350,26 @@ __device__ __forceinline__ MaskKey client_key(uint64_t seed, uint32_t purpose) {
   return K;
 }
 
-// (w3 2^96 + w2 2^64 + w1 2^32 + w0) mod q for q < 2^54: Horner steps of one
-// byte, every intermediate below 2^62.
-__device__ uint64_t mod_q_128(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint64_t q) {
+// (w3 2^96 + w2 2^64 + w1 2^32 + w0) mod q for q < 2^54.  For q = 2^54 -
+// delta: 2^64 = 2^10 delta and 2^96 = 2^42 delta, so the value is the sum of
+// three 64-bit terms, w1:w0, w2 2^10 delta (below 2^64) and w3 2^42 delta =
+// (y mod 2^12) 2^42 + (y >> 12) delta with y = w3 delta, each folded once.
+// Otherwise Horner steps of one byte, every intermediate below 2^62.
+__device__ __forceinline__ uint64_t mod_q_128(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
+                                              const Prime& P) {
+  const uint32_t pd = pm_delta(P.q);
+  if (pd) {
+    constexpr uint64_t low54 = (1ull << 54) - 1;
+    auto fold = [&](uint64_t x) { return mul32x32((uint32_t)(x >> 54), pd) + (x & low54); };
+    const uint64_t y = mul32x32(w3, pd);  // < 2^54
+    return reduce_pm60(fold((uint64_t)w1 << 32 | w0) + fold(mul32x32(w2, pd << 10)) +
+                           ((y & 0xfffull) << 42) + fold((y >> 12) * pd),
+                       pd, P.q);
+  }
   const uint32_t w[4] = {w3, w2, w1, w0};
   uint64_t r = 0;
   for (int a = 0; a < 4; ++a)
-    for (int sh = 24; sh >= 0; sh -= 8) r = ((r << 8) | ((w[a] >> sh) & 0xFFu)) % q;
+    for (int sh = 24; sh >= 0; sh -= 8) r = reduce64((r << 8) | ((w[a] >> sh) & 0xFFu), P.one, P.q);
   return r;
 }
 
@@ -1391,11 +1404,15 @@ k_sample_a(uint64_t seed, uint32_t purpose, int d, int L, int N, long total, Pri
   const MaskKey K = client_key(seed, purpose);
   uint32_t o[16];
   chacha_block(K, (uint32_t)b, (uint32_t)(qd / d), (uint32_t)(qd % d), (uint32_t)l, o);
-  const uint64_t q = ps.p[l].q;
-  uint64_t* row = a + ((size_t)qd * L + l) * N + 4 * b;
+  const Prime& P = ps.p[l];
+  ulonglong2* row = reinterpret_cast<ulonglong2*>(a + ((size_t)qd * L + l) * N + 4 * b);
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
-    row[n] = mod_q_128(o[4 * n], o[4 * n + 1], o[4 * n + 2], o[4 * n + 3], q);
+  for (int n = 0; n < 4; n += 2) {
+    ulonglong2 v;
+    v.x = mod_q_128(o[4 * n], o[4 * n + 1], o[4 * n + 2], o[4 * n + 3], P);
+    v.y = mod_q_128(o[4 * n + 4], o[4 * n + 5], o[4 * n + 6], o[4 * n + 7], P);
+    row[n / 2] = v;
+  }
 }
 
 // Thread per (query x coordinate qd, block b): centred binomial error
@@ -1421,7 +1438,7 @@ k_sample_e(uint64_t seed, uint32_t purpose, int d, int N, long total, int16_t* _
 
 // Workgroup per (query, coordinate, limb): c1 = a, c0 = -a s + e + Delta m.
 template <int LOGN, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T)
+__global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_encrypt(const uint64_t* __restrict__ a_in, const int16_t* __restrict__ e_in,
           const int32_t* __restrict__ msgs, const uint64_t* __restrict__ sk_ntt,
           uint64_t* __restrict__ ct, int L, uint32_t t, PrimeSet ps, TwSet tws) {
@@ -1429,17 +1446,21 @@ k_encrypt(const uint64_t* __restrict__ a_in, const int16_t* __restrict__ e_in,
   constexpr int N = NttShape<LOGN>::N;
   const int tid = threadIdx.x;
   const int b = blockIdx.x;  // (qi d + i) L + l
-  const int l = b % L;
-  const int qd = b / L;      // qi d + i
+  const int l = uniform(b % L);
+  const int qd = uniform(b / L);  // qi d + i
   const Prime& P = ps.p[l];
   const uint64_t* a = a_in + (size_t)b * N;
+  uint64_t* c0 = ct + ((size_t)qd * 2 * L + l) * N;
+  uint64_t* c1 = ct + (((size_t)qd * 2 + 1) * L + l) * N;
   uint64_t v[16];
 #pragma unroll
-  for (int x = 0; x < 16; ++x) v[x] = a[coef_index<LOGN>(tid, x)];
+  for (int x = 0; x < 16; ++x) v[x] = *coef_ptr<LOGN, PM>(a, tid, x);
+#pragma unroll
+  for (int x = 0; x < 16; ++x) *coef_ptr<LOGN, PM>(c1, tid, x) = v[x];
   ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
   for (int x = 0; x < 16; ++x)
-    v[x] = mulmod<PM>(v[x], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, x)], P);
+    v[x] = mulmod<PM>(v[x], *ntt_ptr<LOGN, PM>(sk_ntt + (size_t)l * N, tid, x), P);
   ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
   // message [m]_t as a constant: Delta m in coefficient 0
   const int64_t mraw = msgs[qd];
@@ -1447,18 +1468,13 @@ k_encrypt(const uint64_t* __restrict__ a_in, const int16_t* __restrict__ e_in,
   if (mm < 0) mm += t;
   const uint64_t dm = shoup((uint64_t)mm, P.delta, P.deltap, P.q);
   const int16_t* e = e_in + (size_t)qd * N;
-  uint64_t* c0 = ct + ((size_t)qd * 2 * L + l) * N;
-  uint64_t* c1 = ct + (((size_t)qd * 2 + 1) * L + l) * N;
 #pragma unroll
   for (int x = 0; x < 16; ++x) {
-    const int j = coef_index<LOGN>(tid, x);
-    const int ej = e[j];
-    const uint64_t ev = ej < 0 ? P.q - (uint64_t)(-ej) : (uint64_t)ej;
-    uint64_t r = submod(ev, v[x], P.q);
-    if (j == 0) r = addmod(r, dm, P.q);
-    c0[j] = r;
+    const int ej = *coef_ptr<LOGN, PM>(e, tid, x);
+    uint64_t r = submod(lift_small(ej, P.q), v[x], P.q);
+    if (coef_index<LOGN>(tid, x) == 0) r = addmod(r, dm, P.q);
+    *coef_ptr<LOGN, PM>(c0, tid, x) = r;
   }
-  for (int j = tid; j < N; j += blockDim.x) c1[j] = a[j];
 }
 
 // Multi-word helpers for the exact CRT decode (little-endian 32-bit words).
@@ -1537,47 +1553,48 @@ __device__ __forceinline__ uint32_t crt_round(const uint64_t* xl, int L, const P
   return (uint32_t)((sumA + rnd) % D.t);
 }
 
-// Workgroup per ciphertext: x_l = INTT(NTT(c1) NTT(s)) + c0 per limb, then the
-// exact decode and the client share [m + ||q||^2]_t.
+// Workgroup per (ciphertext, limb): x_l = INTT(NTT(c1) NTT(s)) + c0, x[M][L][N].
+// (A workgroup per ciphertext, walking the limbs and decoding, took 177 us for
+// the 123 ciphertexts of a million-point answer: fewer workgroups than CUs,
+// each with 256 registers per thread.)
 template <int LOGN, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T)
+__global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
 k_decrypt(const uint64_t* __restrict__ ct, const uint64_t* __restrict__ sk_ntt,
-          const uint32_t* __restrict__ qnorm2, uint32_t* __restrict__ outp, int L,
-          PrimeSet ps, TwSet tws, DecodeConst D) {
+          uint64_t* __restrict__ xout, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
   constexpr int N = NttShape<LOGN>::N;
-  const int tid = threadIdx.x, m = blockIdx.x;
-  uint64_t x[kMaxLimbs][16];
-  for (int l = 0; l < L; ++l) {
-    const Prime& P = ps.p[l];
-    const uint64_t* c0 = ct + (((size_t)m * 2) * L + l) * N;
-    const uint64_t* c1 = ct + (((size_t)m * 2 + 1) * L + l) * N;
-    uint64_t v[16];
+  const int tid = threadIdx.x, l = uniform(blockIdx.x % L), m = uniform(blockIdx.x / L);
+  const Prime& P = ps.p[l];
+  const uint64_t* c0 = ct + (((size_t)m * 2) * L + l) * N;
+  const uint64_t* c1 = ct + (((size_t)m * 2 + 1) * L + l) * N;
+  uint64_t* x = xout + (size_t)blockIdx.x * N;
+  uint64_t v[16];
 #pragma unroll
-    for (int a = 0; a < 16; ++a) v[a] = c1[coef_index<LOGN>(tid, a)];
-    ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
+  for (int a = 0; a < 16; ++a) v[a] = *coef_ptr<LOGN, PM>(c1, tid, a);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
 #pragma unroll
-    for (int a = 0; a < 16; ++a)
-      v[a] = mulmod<PM>(v[a], sk_ntt[(size_t)l * N + ntt_slot<LOGN>(tid, a)], P);
-    ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
+  for (int a = 0; a < 16; ++a)
+    v[a] = mulmod<PM>(v[a], *ntt_ptr<LOGN, PM>(sk_ntt + (size_t)l * N, tid, a), P);
+  ntt_inv<LOGN, PM>(v, lds, tid, tws.tw[l] + N, P);
 #pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      const uint64_t r = addmod(v[a], c0[coef_index<LOGN>(tid, a)], P.q);
+  for (int a = 0; a < 16; ++a)
+    *coef_ptr<LOGN, PM>(x, tid, a) = addmod(v[a], *coef_ptr<LOGN, PM>(c0, tid, a), P.q);
+}
+
+// Thread per coefficient: the exact decode of x[m][.][j] and the client share
+// [m + ||q||^2]_t.
+__global__ void __launch_bounds__(256)
+k_decode(const uint64_t* __restrict__ x, const uint32_t* __restrict__ qnorm2,
+         uint32_t* __restrict__ outp, int L, int logN, long total, PrimeSet ps, DecodeConst D) {
+  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= total) return;
+  const long m = g >> logN, j = g & ((1l << logN) - 1);
+  uint64_t xl[kMaxLimbs];
 #pragma unroll
-      for (int ll = 0; ll < kMaxLimbs; ++ll)
-        if (ll == l) x[ll][a] = r;
-    }
-  }
-  const uint32_t qn = qnorm2 ? qnorm2[m] : 0u;
-#pragma unroll
-  for (int a = 0; a < 16; ++a) {
-    uint64_t xl[kMaxLimbs];
-#pragma unroll
-    for (int l = 0; l < kMaxLimbs; ++l) xl[l] = x[l][a];
-    const uint32_t mm = crt_round(xl, L, ps, D);
-    const uint64_t s = (uint64_t)mm + qn;
-    outp[(size_t)m * N + coef_index<LOGN>(tid, a)] = (uint32_t)(s >= D.t ? s - D.t : s);
-  }
+  for (int l = 0; l < kMaxLimbs; ++l)
+    xl[l] = l < L ? x[((m * L + l) << logN) + j] : 0;
+  const uint64_t s = (uint64_t)crt_round(xl, L, ps, D) + (qnorm2 ? qnorm2[m] : 0u);
+  outp[g] = (uint32_t)(s >= D.t ? s - D.t : s);
 }
 
 // --------------------------------------------------------------------------
@@ -2099,20 +2116,23 @@ hipError_t launch_encrypt(const uint64_t* a, const int16_t* e, const int32_t* ms
 }
 
 hipError_t launch_decrypt(const uint64_t* ct, int M, const uint64_t* sk_ntt,
-                          const uint32_t* qnorm2, uint32_t* out, int L, int logN,
+                          const uint32_t* qnorm2, uint64_t* x, uint32_t* out, int L, int logN,
                           const PrimeSet& ps, const TwSet& tws, const DecodeConst& D,
                           hipStream_t st) {
   if (M <= 0) return hipSuccess;
   switch (logN) {
-#define SANNS_CASE(LG)                                                                   \
-  case LG:                                                                               \
-    ntt_launch<LG>(SANNS_PM(k_decrypt, LG), (unsigned)M, st, ct, sk_ntt, qnorm2, out, L, ps, tws, D); \
+#define SANNS_CASE(LG)                                                                     \
+  case LG:                                                                                 \
+    ntt_launch<LG>(SANNS_PM(k_decrypt, LG), (unsigned)(M * L), st, ct, sk_ntt, x, L, ps, tws); \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
     default:
       return hipErrorInvalidValue;
   }
+  const long total = (long)M << logN;
+  hipLaunchKernelGGL(k_decode, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, x, qnorm2,
+                     out, L, logN, total, ps, D);
   return hipGetLastError();
 }
 

@@ -159,8 +159,9 @@ hipError_t launch_intt_mask_cp(uint64_t* ct, const uint32_t* share, const uint32
 hipError_t launch_encrypt(const uint64_t* a, const int16_t* e, const int32_t* msgs,
                           const uint64_t* sk_ntt, uint64_t* ct, int Qd, int L, int logN,
                           uint32_t t, const PrimeSet& ps, const TwSet& tws, hipStream_t st);
+// x: scratch for the residues before the decode, [M][L][N].
 hipError_t launch_decrypt(const uint64_t* ct, int M, const uint64_t* sk_ntt,
-                          const uint32_t* qnorm2, uint32_t* out, int L, int logN,
+                          const uint32_t* qnorm2, uint64_t* x, uint32_t* out, int L, int logN,
                           const PrimeSet& ps, const TwSet& tws, const DecodeConst& D,
                           hipStream_t st);
 hipError_t launch_mult_plain(const uint2* cq, const uint2* db, int i, int k, int d, int C,

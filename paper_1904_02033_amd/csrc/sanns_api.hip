@@ -681,12 +681,21 @@ extern "C" sanns_status sanns_decrypt_shares(sanns_ctx* ctx, const int8_t* sk,
   HIP_TRY(hipSetDevice(ctx->device));
   hipStream_t st = (hipStream_t)stream;
   const uint32_t N = ctx->p.N, L = ctx->p.L;
+  // the secret key's NTT form and the residues of a batch of ciphertexts (at
+  // most 64 MiB of them, which also keeps the decode's reads in cache)
+  const size_t poly = (size_t)L * N;
+  const uint32_t batch = (uint32_t)std::min<size_t>(M, std::max<size_t>(1, (64u << 20) / (poly * 8)));
   uint64_t* sk_ntt = nullptr;
-  HIP_TRY(hipMallocAsync((void**)&sk_ntt, (size_t)L * N * 8, st));
-  HIP_TRY(launch_sk_ntt(sk, sk_ntt, ctx->logN, (int)L, ctx->ps, ctx->tws, st));
-  HIP_TRY(launch_decrypt(ct, (int)M, sk_ntt, qnorm2, client_share, (int)L, ctx->logN, ctx->ps,
-                         ctx->tws, ctx->dec, st));
-  HIP_TRY(hipFreeAsync(sk_ntt, st));
+  HIP_TRY(hipMallocAsync((void**)&sk_ntt, (1 + (size_t)batch) * poly * 8, st));
+  hipError_t err = launch_sk_ntt(sk, sk_ntt, ctx->logN, (int)L, ctx->ps, ctx->tws, st);
+  for (uint32_t m0 = 0; m0 < M && err == hipSuccess; m0 += batch)
+    err = launch_decrypt(ct + m0 * 2 * poly, (int)std::min(batch, M - m0), sk_ntt,
+                         qnorm2 ? qnorm2 + m0 : nullptr, sk_ntt + poly,
+                         client_share + (size_t)m0 * N, (int)L, ctx->logN, ctx->ps, ctx->tws,
+                         ctx->dec, st);
+  const hipError_t ferr = hipFreeAsync(sk_ntt, st);
+  HIP_TRY(err);
+  HIP_TRY(ferr);
   return SANNS_OK;
 }
 
