@@ -639,6 +639,98 @@ k_mac(const uint2* __restrict__ qntt, const uint2* __restrict__ db,
                                  C, ps, out);
 }
 
+// One query against few chunks, where k_mac's grid leaves the chip idle and its
+// time is one thread's chain of d dependent loads: a workgroup takes 64 slots x
+// CT chunks, its four waves a quarter of the coordinates each with four
+// coordinates in flight ahead of the multiplies, and the four partial residues
+// are added through LDS.  The chunk tile runs fastest inside contiguous per-XCD
+// ranges, so that the tiles which share the query's operands find them in one
+// L2.
+template <int CT>
+__global__ void __launch_bounds__(256)
+k_mac_split(const uint2* __restrict__ qntt, const uint2* __restrict__ db, int d, int L, int logN,
+            int C, int n_blocks, PrimeSet ps, uint64_t* __restrict__ out) {
+  constexpr int U = 4;
+  __shared__ uint64_t red[4][2 * CT][64];
+  const int per_xcd = (n_blocks + 7) >> 3;
+  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (lin >= n_blocks) return;
+  const int N = 1 << logN, nsr = N >> 6, nkt = (C + CT - 1) / CT;
+  const int k0 = (lin % nkt) * CT, sr = (lin / nkt) % nsr, l = lin / nkt / nsr;
+  const int s = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const Prime& P = ps.p[l];
+  const int b0 = (int)((long)g * d / 4), b1 = (int)((long)(g + 1) * d / 4);
+  const uint2* qb = qntt + (size_t)l * N + 64 * sr + s;
+  const uint2* dbb[CT];
+#pragma unroll
+  for (int b = 0; b < CT; ++b)
+    dbb[b] = db + (((size_t)l * C + (k0 + b < C ? k0 + b : C - 1)) * d) * N + 64 * sr + s;
+  uint64_t res[2][CT];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int b = 0; b < CT; ++b) res[c][b] = 0;
+  uint2 x[U][2], y[U][CT];
+  // operands of coordinates i .. i + U - 1; those at or past `end` are the
+  // last one's with a zero query residue
+  auto load = [&](int i, int end) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ii = i + u < end ? i + u : end - 1;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) x[u][c] = qb[((size_t)ii * 2 + c) * L * N];
+#pragma unroll
+      for (int b = 0; b < CT; ++b) y[u][b] = dbb[b][(size_t)ii * N];
+    }
+  };
+  for (int i0 = b0; i0 < b1; i0 += 252) {  // at most 255 products per sum
+    const int i1 = i0 + 252 < b1 ? i0 + 252 : b1;
+    Acc3 acc[2][CT];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int b = 0; b < CT; ++b) acc3_zero(acc[c][b]);
+    load(i0, i1);
+    for (int i = i0; i < i1; i += U) {
+      uint2 xc[U][2], yc[U][CT];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) xc[u][c] = i + u < i1 ? x[u][c] : make_uint2(0u, 0u);
+#pragma unroll
+        for (int b = 0; b < CT; ++b) yc[u][b] = y[u][b];
+      }
+      if (i + U < i1) load(i + U, i1);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int b = 0; b < CT; ++b)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            acc[c][b].lo += mul32x32(xc[u][c].x, yc[u][b].x);
+            acc[c][b].hi += mul32x32(xc[u][c].y, yc[u][b].y);
+            acc[c][b].mid += mul32x32(xc[u][c].x + xc[u][c].y, yc[u][b].x + yc[u][b].y);
+          }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int b = 0; b < CT; ++b)
+        res[c][b] = addmod(res[c][b], acc3_reduce(acc[c][b], P), P.q);
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int b = 0; b < CT; ++b) red[g][2 * b + c][s] = res[c][b];
+  __syncthreads();
+  for (int r = g; r < 2 * CT; r += 4) {
+    const int k = k0 + r / 2;
+    if (k >= C) continue;
+    const uint64_t v = red[0][r][s] + red[1][r][s] + red[2][r][s] + red[3][r][s];
+    out[(((size_t)k * 2 + (r & 1)) * L + l) * N + 64 * sr + s] = csub(csub(v, 2 * P.q), P.q);
+  }
+}
+
 // LDS-staged multiply-accumulate for the every-query-against-every-chunk
 // schedule of a batch.  A block owns S slots of one limb, a tile of QB = QG QT
 // queries and CB = CG CT chunks; per step of DI coordinates it stages the
@@ -1775,6 +1867,37 @@ static hipError_t launch_mac_t(const uint2* qntt, const uint2* db, const void* t
                        qntt, db, (const MacTile<QT, CT>*)tiles, n_tiles, Q, d, L, logN, C,
                        (int)nb, ps, out);
   return hipGetLastError();
+}
+
+template <int CT>
+static hipError_t launch_mac_split_t(const uint2* qntt, const uint2* db, int d, int L, int logN,
+                                     int C, const PrimeSet& ps, uint64_t* out, hipStream_t st) {
+  const int nb = ((1 << logN) >> 6) * ((C + CT - 1) / CT) * L;
+  hipLaunchKernelGGL(k_mac_split<CT>, dim3((unsigned)((nb + 7) / 8 * 8)), dim3(256), 0, st, qntt,
+                     db, d, L, logN, C, nb, ps, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_mac_split(int ct, const uint2* qntt, const uint2* db, int d, int L, int logN,
+                            int C, const PrimeSet& ps, uint64_t* out, hipStream_t st) {
+  switch (ct) {
+    case 1: return launch_mac_split_t<1>(qntt, db, d, L, logN, C, ps, out, st);
+    case 2: return launch_mac_split_t<2>(qntt, db, d, L, logN, C, ps, out, st);
+    case 4: return launch_mac_split_t<4>(qntt, db, d, L, logN, C, ps, out, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// The largest tile whose workgroups are at least two for each of the 256 CUs
+// (else 1), and only while k_mac's own 1 x 8 tiles, in workgroups of 256 slots,
+// are not: from there on k_mac streams the database.
+int mac_split_tile(int logN, int C, int L) {
+  if (logN < 6) return 0;
+  const long N = 1l << logN;
+  if ((N < 256 ? 1 : N / 256) * ((C + 7) / 8) * L >= 512) return 0;
+  for (int ct = 4; ct > 1; ct /= 2)
+    if ((N >> 6) * ((C + ct - 1) / ct) * L >= 512) return ct;
+  return 1;
 }
 
 size_t mac_tile_bytes(int QT, int CT) {

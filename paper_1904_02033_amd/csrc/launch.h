@@ -28,6 +28,13 @@ hipError_t launch_mac(int QT, int CT, const uint2* qntt, const uint2* db, const 
                       int n_tiles, int Q, int d, int L, int logN, int C, const PrimeSet& ps,
                       uint64_t* out, hipStream_t st);
 size_t mac_tile_bytes(int QT, int CT);  // 0 for a shape that is not built
+// One query against C chunks with the coordinates split over a workgroup's
+// waves, in tiles of ct = 1, 2 or 4 chunks; mac_split_tile gives the tile where
+// that form is the faster one, 0 where launch_mac's is.
+constexpr int kMacSplit = 90;  // + ct: the form's internal schedule id
+hipError_t launch_mac_split(int ct, const uint2* qntt, const uint2* db, int d, int L, int logN,
+                            int C, const PrimeSet& ps, uint64_t* out, hipStream_t st);
+int mac_split_tile(int logN, int C, int L);
 
 // LDS-staged variants of the all-pairs multiply-accumulate:
 // X(id, QT, CT, QG, CG, S, DI, UNR), block = S slots x QG x CG threads

@@ -222,6 +222,9 @@ void choose_shape(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool
     // query (the clustered form's cluster chunks): 1 x 8 measured fastest
     qt = 1;
     ct = 8;
+    // few chunks: the split form (its tile replaces 1 x 8)
+    const int sp = regular && Q == 1 ? mac_split_tile(ctx->logN, (int)C, (int)ctx->p.L) : 0;
+    if (sp) lds = kMacSplit + sp;
   } else {
     qt = 2;
     ct = 4;
@@ -765,7 +768,10 @@ sanns_status enqueue_fused(sanns_ctx* ctx, const sanns_db* db, const uint64_t* c
     const int8_t* dig = (const int8_t*)db->mem + (size_t)L * C * d * N * 8 + (size_t)C * N * 4;
     HIP_TRY(launch_mac_mfma(qdig, dig, (int)Q, (int)d, (int)C, (int)L, ctx->logN, ctx->ds,
                             sums, st));
-  } else if (lds > 0)
+  } else if (lds > kMacSplit)
+    HIP_TRY(launch_mac_split(lds - kMacSplit, (const uint2*)qntt, res, (int)d, (int)L, ctx->logN,
+                             (int)C, ctx->ps, ct_out, st));
+  else if (lds > 0)
     HIP_TRY(launch_mac_lds(lds, (const uint2*)qntt, res, (int)Q, (int)d, (int)L, ctx->logN,
                            (int)C, ctx->ps, ct_out, st));
   else
