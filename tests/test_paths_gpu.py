@@ -1,0 +1,203 @@
+"""The launch rules' branches at the sizes where they change: transforms of
+polynomials in pairs or alone, one query against few chunks with the
+coordinates split over a workgroup's waves, point rows gathered 16, 4 or 1
+bytes at a time, decryption in batches, seeded encryption under primes away
+from 2^54, and the k-means kernels at the edges of their tiles.  Every value is
+an integer: equality throughout."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import balance as obal
+from problem import make_problem, true_distances
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mods():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1904_02033_amd import native as nat, stage
+    return nat, stage
+
+
+def _dev(x, dtype=None):
+    t = torch.as_tensor(np.ascontiguousarray(x))
+    return (t.to(dtype) if dtype is not None else t).cuda()
+
+
+def _ctx(nat, stage, N, qs, t, flags=0):
+    p = nat.sanns_params()
+    p.N, p.L, p.t = N, len(qs), t
+    for l, q in enumerate(qs):
+        p.q[l] = q
+    p.flags = nat.SANNS_FLAG_INSECURE_TEST | flags
+    return stage.Context(params=p)
+
+
+def _seeded(nat, stage, N, L, n, d, Q, seed):
+    """A context, an encoded database and seeded queries, all on the device."""
+    qs, t = oracle.rns_primes(N, L), oracle.plain_modulus(N, 27)
+    ctx = _ctx(nat, stage, N, qs, t)
+    g = np.random.default_rng(seed)
+    pts = g.integers(0, 256, (n, d)).astype(np.uint8)
+    que = g.integers(0, 256, (Q, d)).astype(np.uint8)
+    slot = stage.linear_slot_map(n, N, g.permutation(n))
+    db = stage.encode_db(ctx, pts, slot)
+    sk = stage.keygen(ctx, seed)
+    ct = stage.encrypt_query_seeded(ctx, sk, _dev(que.astype(np.int32)), seed + 1)
+    ids = _dev(np.arange(Q, dtype=np.uint64) + np.uint64(seed))
+    return ctx, db, sk, ct, ids, pts, que, slot
+
+
+def _run(stage, ctx, db, ct, ids, mode, schedule=(0, 0)):
+    ctx.set_schedule(*schedule)
+    out, share = stage.Distances(ctx, db, ct.shape[0], mode=mode).run(ct, b"k" * 32, ids)
+    torch.cuda.synchronize()
+    ctx.device_status()
+    ctx.set_schedule()
+    return out, share
+
+
+def _check_distances(stage, ctx, sk, out, share, pts, que, slot, C):
+    qn = (que.astype(np.int64) ** 2).sum(1) % ctx.t
+    client = stage.decrypt_shares(ctx, sk, out, _dev(np.repeat(qn, C).astype(np.uint32)))
+    tot = (client.cpu().numpy().astype(np.int64) + share.cpu().numpy()) % ctx.t
+    for m in range(len(tot)):
+        ids = slot[m % C * ctx.N:(m % C + 1) * ctx.N]
+        real = ids >= 0
+        assert (tot[m][real] == oracle.sqdist(que[m // C], pts[ids[real]])).all(), m
+
+
+# 2 L Q d and 2 L Q C polynomials on both sides of 1,024, above it odd counts
+# of encoded rows too; the persistent form transforms one polynomial at a time
+@pytest.mark.parametrize("N,L,Q,d,C", [(4096, 2, 8, 33, 33), (8192, 3, 8, 23, 22),
+                                       (16384, 4, 7, 19, 19), (4096, 2, 8, 31, 31)])
+def test_pair_transforms(mods, N, L, Q, d, C):
+    nat, stage = mods
+    ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 5, d, Q, 10 + d)
+    out, share = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED)
+    po, psh = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_PERSISTENT)
+    assert torch.equal(out.view(torch.int64), po.view(torch.int64))
+    assert torch.equal(share.view(torch.int32), psh.view(torch.int32))
+    _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+
+
+@pytest.mark.parametrize("N,L", [(64, 1), (256, 2), (4096, 2), (8192, 3)])
+@pytest.mark.parametrize("d", [1, 3, 4, 5, 130, 1013])
+def test_split_coordinates_one_query(mods, N, L, d):
+    nat, stage = mods
+    for C in (1, 3, 9) if d < 1000 else (2,):
+        ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 3, d, 1, d + C)
+        out, share = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED)
+        go, gs = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED, (1, 1))
+        assert torch.equal(out.view(torch.int64), go.view(torch.int64)), (d, C)
+        assert torch.equal(share.view(torch.int32), gs.view(torch.int32))
+        if L > 1:  # (one 54-bit prime does not hold the noise)
+            _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+        ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.int8])
+@pytest.mark.parametrize("d", [7, 20, 32])
+def test_gather_widths(mods, d, dtype):
+    """Rows at every alignment give the same database, padding slots too."""
+    nat, stage = mods
+    N, n = 256, 700
+    ctx = _ctx(nat, stage, N, oracle.rns_primes(N, 2), oracle.plain_modulus(N, 27))
+    g = np.random.default_rng(d)
+    pts = g.integers(np.iinfo(dtype).min, np.iinfo(dtype).max + 1, (n, d)).astype(dtype)
+    slot = np.full(3 * N, -1, dtype=np.int64)
+    slot[g.permutation(3 * N)[:n]] = np.arange(n)
+    used = 2 * 3 * d * N * 8 + 3 * N * 4
+    want = None
+    for off in (0, 4, 1):
+        buf = torch.zeros(n * d + 16, dtype=torch.uint8, device="cuda")
+        view = buf[off:off + n * d]
+        view.copy_(torch.as_tensor(pts.view(np.uint8).reshape(-1)))
+        db = stage.encode_db(ctx, view.view(torch.int8 if dtype == np.int8 else torch.uint8)
+                             .view(n, d), slot)
+        mem = db.mem[:used].cpu()
+        assert want is None or torch.equal(mem, want), off
+        want = mem
+    norms = want[-3 * N * 4:].numpy().view(np.uint32)
+    ref = np.where(slot >= 0, (pts.astype(np.int64) ** 2).sum(1)[np.maximum(slot, 0)], 0)
+    assert (norms == ref).all()
+
+
+def test_decrypt_batches(mods):
+    """1,025 ciphertexts of 64 KiB residues: one more than a batch holds."""
+    nat, stage = mods
+    N, L, M = 4096, 2, 1025
+    qs = oracle.rns_primes(N, L)
+    ctx = _ctx(nat, stage, N, qs, oracle.plain_modulus(N, 25))
+    sk = stage.keygen(ctx, 3)
+    ct = torch.randint(0, min(qs), (M, 2, L, N), device="cuda").view(torch.uint64)
+    qn = torch.arange(M, dtype=torch.int32, device="cuda").view(torch.uint32)
+    got = stage.decrypt_shares(ctx, sk, ct, qn).cpu().numpy()
+    for m in (0, 511, 1023, 1024):
+        one = ct.view(torch.int64)[m:m + 1].contiguous().view(torch.uint64)
+        alone = stage.decrypt_shares(ctx, sk, one, qn.view(torch.int32)[m:m + 1].view(torch.uint32))
+        assert (alone.cpu().numpy()[0] == got[m]).all(), m
+
+
+def test_seeded_encryption_general_primes(mods):
+    nat, stage = mods
+    N, Q, d = 4096, 2, 3
+    qs = oracle.rns_primes(N, 1, bits=50) + oracle.rns_primes(N, 1)
+    P = oracle.Params(N, qs, oracle.plain_modulus(N, 25))
+    ctx = _ctx(nat, stage, N, qs, P.t)
+    sk = stage.keygen(ctx, 5)
+    msgs = np.arange(Q * d, dtype=np.int32).reshape(Q, d) - 2
+    ct = stage.encrypt_query_seeded(ctx, sk, _dev(msgs), 77).cpu().numpy()
+    s = oracle.sample_secret(5, N)
+    a, e = oracle.sample_encryption(P, 77, Q, d)
+    for q in range(Q):
+        want = oracle.encrypt_constants(P, s, a[q], e[q], [int(x) for x in msgs[q]])
+        assert (ct[q] == want).all()
+
+
+@pytest.mark.parametrize("d", [1, 31, 33, 64, 65, 96, 97, 128, 160, 255, 256])
+@pytest.mark.parametrize("n,k", [(1, 1), (255, 15), (257, 16), (300, 65), (513, 129)])
+def test_kmeans_tile_edges(mods, n, d, k):
+    """Extreme coordinates and centres (the largest norms and products),
+    duplicate centres (ties), odd d (bytes and word rows)."""
+    nat, _ = mods
+    g = np.random.default_rng(n + d + k)
+    X = g.integers(-128, 128, (n, d)).astype(np.int8)
+    X[0], X[-1] = -128, 127
+    C = g.integers(-128 * 256, 127 * 256 + 1, (k, d)).astype(np.int32)
+    C[0] = -128 * 256
+    if k > 2:
+        C[k - 1], C[k // 2] = 127 * 256, C[0]
+    Xd, Cd = _dev(X), _dev(C)
+    ws = torch.empty(nat.sanns_kmeans_workspace(k, d), dtype=torch.uint8, device="cuda")
+    a = torch.empty(n, dtype=torch.int32, device="cuda")
+    nat.sanns_kmeans_assign(Xd.data_ptr(), n, d, Cd.data_ptr(), k, 0, a.data_ptr(), 0,
+                            ws.data_ptr(), ws.numel(), 0)
+    want = obal.assign(X, C)
+    assert (a.cpu().numpy() == want).all()
+    nat.sanns_kmeans_update(Xd.data_ptr(), n, d, a.data_ptr(), k, Cd.data_ptr(), 0,
+                            ws.data_ptr(), ws.numel(), 0)
+    assert (Cd.cpu().numpy() == obal.update(X, want, C)).all()
+
+
+@pytest.mark.parametrize("n", [(1 << 32) // 255 - 1, (1 << 32) // 255 + 1])
+def test_kmeans_update_many_points(mods, n):
+    """Both forms of the sums: two coordinates per add, and one where their
+    halves could carry; every point of one cluster at the largest coordinate."""
+    nat, _ = mods
+    d, k = 3, 2
+    X = torch.full((n, d), 127, dtype=torch.int8, device="cuda")
+    X[0] = -128
+    a = torch.zeros(n, dtype=torch.int32, device="cuda")
+    C = torch.full((k, d), 7, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(k, dtype=torch.int64, device="cuda")
+    ws = torch.empty(nat.sanns_kmeans_workspace(k, d), dtype=torch.uint8, device="cuda")
+    nat.sanns_kmeans_update(X.data_ptr(), n, d, a.data_ptr(), k, C.data_ptr(), cnt.data_ptr(),
+                            ws.data_ptr(), ws.numel(), 0)
+    s = 127 * (n - 1) - 128
+    assert C[0].tolist() == [(512 * s + n) // (2 * n)] * d and C[1].tolist() == [7] * d
+    assert cnt.tolist() == [n, 0]
