@@ -329,7 +329,7 @@ sanns_status sanns_distances(sanns_ctx *ctx, const sanns_db *db,
  *   ct_in, query_ids, mask_key as sanns_distances;
  *   ct_out     dev [M + Q Ct][2][L][N], server_share dev [M + Q Ct][N];
  *   workspace  dev, sanns_distances_gathered_workspace(ctx, d, Q, M, tail)
- *              bytes (the tail's residues are copied into it).
+ *              bytes;
  * The chunk word of the mask nonce is m for gathered chunk m and M + k for
  * tail chunk k, so a (mask_key, query id) pair must not be reused across
  * calls.  A slot index outside [-1, n) is taken as padding and a share (or

@@ -1284,47 +1284,83 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
 // database encoding
 // --------------------------------------------------------------------------
 
-// Thread per slot: gathers the slot's point into the transposed plaintext
-// buffer gt[k][i][j] = -2 p[i] (int16) and writes [||p||^2] to norms.
-// Slots [base, base + total) of the database; gt is local to that range.
+// W bytes of a point's row in one load (W = 16, 4 or 1).
+template <int W>
+struct RowBytes {
+  uint32_t w[W / 4];
+  __device__ __forceinline__ void load(const uint8_t* p) {
+    if constexpr (W == 16) {
+      const uint4 v = *reinterpret_cast<const uint4*>(p);
+      w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+    } else {
+      w[0] = *reinterpret_cast<const uint32_t*>(p);
+    }
+  }
+  __device__ __forceinline__ int get(int b) const { return (int)((w[b / 4] >> (8 * (b % 4))) & 255u); }
+};
+template <>
+struct RowBytes<1> {
+  int x;
+  __device__ __forceinline__ void load(const uint8_t* p) { x = *p; }
+  __device__ __forceinline__ int get(int) const { return x; }
+};
+
+// Thread per two consecutive slots: gathers their points into the transposed
+// plaintext buffer gt[k][i][j] = -2 p[i] (int16, two slots per store) and
+// writes [||p||^2] to norms.  Slots [base, base + total) of the database; gt is
+// local to that range.  A point's row is read W bytes at a time (d % W == 0,
+// rows aligned to W): a
+// byte at a time the loads bound it (25 chunks of 128 coordinates 150 us; 16 bytes
+// at a time 25 us).
+template <int W>
 __global__ void __launch_bounds__(256)
 k_gather(const uint8_t* __restrict__ pts, int is_signed, long n, int d,
          const int64_t* __restrict__ slot_point, long base, long total, int logN,
          int16_t* __restrict__ gt, uint32_t* __restrict__ norms, uint32_t* err) {
-  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= total) return;
+  const long g = 2 * ((long)blockIdx.x * blockDim.x + threadIdx.x);
+  if (g >= total) return;  // total is a multiple of N
   const int N = 1 << logN;
   const long k = g >> logN;
   const int j = (int)(g & (N - 1));
-  long pid = slot_point[base + g];
-  if (pid >= n || pid < -1) {
-    if (err) atomicOr(err, 2u);
-    pid = -1;
+  const uint8_t* row[2];
+  bool real[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const long pid = slot_point[base + g + s];
+    if ((pid >= n || pid < -1) && err) atomicOr(err, 2u);
+    real[s] = pid >= 0 && pid < n;
+    row[s] = pts + (real[s] ? (size_t)pid * d : 0);
   }
-  int16_t* col = gt + (size_t)k * d * N + j;
-  uint32_t nrm = 0;
-  if (pid < 0) {
-    for (int i = 0; i < d; ++i) col[(size_t)i * N] = 0;
-  } else {
-    const uint8_t* row = pts + (size_t)pid * d;
-    for (int i = 0; i < d; ++i) {
-      const int x = is_signed ? (int)(int8_t)row[i] : (int)row[i];
-      col[(size_t)i * N] = (int16_t)(-2 * x);
-      nrm += (uint32_t)(x * x);
+  uint32_t* col = reinterpret_cast<uint32_t*>(gt + (size_t)k * d * N + j);
+  uint32_t nrm[2] = {0, 0};
+  for (int i0 = 0; i0 < d; i0 += W) {
+    RowBytes<W> v[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) v[s].load(row[s] + i0);
+#pragma unroll
+    for (int b = 0; b < W; ++b) {
+      uint32_t o = 0;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int u = real[s] ? v[s].get(b) : 0;
+        const int x = is_signed ? (int)(int8_t)u : u;
+        nrm[s] += (uint32_t)(x * x);
+        o |= (uint32_t)(uint16_t)(int16_t)(-2 * x) << (16 * s);
+      }
+      col[(size_t)(i0 + b) * (N / 2)] = o;
     }
   }
-  norms[base + g] = nrm;
+  norms[base + g] = nrm[0];
+  norms[base + g + 1] = nrm[1];
 }
 
-// Gathered chunks of one call (per-query chunks of retrieved points): as
-// k_gather, into 32-bit plaintext coefficients, for kind 0 / 1 (uint8 /
-// int8 points: -2 p[i] and ||p||^2) or kind 2: the server's additive shares
-// p_s in [0, t) of secret-shared points and of their squared norms, where the
-// coefficient is the centred representative of -2 p_s mod t in
-// (-t/2, t/2] and the norm plane holds the norm share.  A share >= t sets
-// error bit 8 and is taken as 0.
+// Gathered chunks of secret-shared points: as k_gather, into 32-bit plaintext
+// coefficients, from the server's additive shares p_s in [0, t) of the points
+// and of their squared norms: the coefficient is the centred representative of
+// -2 p_s mod t in (-t/2, t/2] and the norm plane holds the norm share.  A share
+// >= t sets error bit 8 and is taken as 0.
 __global__ void __launch_bounds__(256)
-k_gather32(const void* __restrict__ pts, int kind, long n, int d,
+k_gather32(const uint32_t* __restrict__ pts, long n, int d,
            const uint32_t* __restrict__ norm_shares, uint32_t t,
            const int64_t* __restrict__ slot_point, long base, long total, int logN,
            int32_t* __restrict__ gt, uint32_t* __restrict__ norms, uint32_t* err) {
@@ -1343,8 +1379,8 @@ k_gather32(const void* __restrict__ pts, int kind, long n, int d,
   bool bad = false;
   if (pid < 0) {
     for (int i = 0; i < d; ++i) col[(size_t)i * N] = 0;
-  } else if (kind == 2) {
-    const uint32_t* row = reinterpret_cast<const uint32_t*>(pts) + (size_t)pid * d;
+  } else {
+    const uint32_t* row = pts + (size_t)pid * d;
     for (int i = 0; i < d; ++i) {
       uint32_t x = row[i];
       if (x >= t) {
@@ -1361,46 +1397,35 @@ k_gather32(const void* __restrict__ pts, int kind, long n, int d,
       bad = true;
       nrm = 0;
     }
-  } else {
-    const uint8_t* row = reinterpret_cast<const uint8_t*>(pts) + (size_t)pid * d;
-    for (int i = 0; i < d; ++i) {
-      const int x = kind == 1 ? (int)(int8_t)row[i] : (int)row[i];
-      col[(size_t)i * N] = -2 * x;
-      nrm += (uint32_t)(x * x);
-    }
   }
   if (bad && err) atomicOr(err, 8u);
   norms[base + g] = nrm;
 }
 
-// Workgroup per (limb, NP consecutive rows (k, i)) with k in [k0, k0 + nk):
-// lift the signed plaintext rows mod q_l, forward NTT, store as 27-bit halves
-// (an odd last row is paired with itself and stored once).
-template <int LOGN, typename G, int NP, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, 4)
+// Workgroup per (l, k, i) with k in [k0, k0 + nk): lift the signed plaintext
+// row mod q_l, forward NTT, store as 27-bit halves.  One polynomial per
+// workgroup: with next to nothing read, the stores of one workgroup overlap the
+// products of the others, and a pair of rows (128 registers and spills) was no
+// faster (9,600 rows of N = 8192: 0.225 ms, in pairs 0.259 ms; 0.329 ms with the
+// general products).
+template <int LOGN, typename G, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, PM ? 6 : 4)
 k_encode_ntt(const G* __restrict__ gt, uint2* __restrict__ dbres, int k0, int nk, int C,
              int d, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
   constexpr int N = NttShape<LOGN>::N;
   const int tid = threadIdx.x;
-  const int rows = nk * d, per = (rows + NP - 1) / NP;
-  const int l = uniform((int)blockIdx.x / per), r0 = uniform(NP * ((int)blockIdx.x % per));
+  const int rows = nk * d;
+  const int l = uniform((int)blockIdx.x / rows), r = uniform((int)blockIdx.x % rows);
   const Prime& P = ps.p[l];
-  uint64_t v[NP][16];
+  const G* src = gt + (size_t)r * N;
+  uint64_t v[16];
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const G* src = gt + (size_t)(r0 + j < rows ? r0 + j : r0) * N;
+  for (int a = 0; a < 16; ++a) v[a] = lift_coef<PM>(*coef_ptr<LOGN, PM>(src, tid, a), P.q);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
+  uint64_t* dst = reinterpret_cast<uint64_t*>(dbres) + (((size_t)l * C + k0) * d + r) * N;
 #pragma unroll
-    for (int a = 0; a < 16; ++a) v[j][a] = lift_coef<PM>(*coef_ptr<LOGN, PM>(src, tid, a), P.q);
-  }
-  ntt_fwd<LOGN, PM, NP>(v, lds, tid, tws.tw[l], P);
-#pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    if (r0 + j >= rows) break;
-    uint64_t* dst = reinterpret_cast<uint64_t*>(dbres) + (((size_t)l * C + k0) * d + r0 + j) * N;
-#pragma unroll
-    for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[j][a]);
-  }
+  for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[a]);
 }
 
 // --------------------------------------------------------------------------
@@ -2060,9 +2085,19 @@ hipError_t launch_persistent(int shape, const PersistArgs& A, const PrimeSet& ps
 hipError_t launch_gather(const void* pts, int is_signed, long n, int d,
                          const int64_t* slot_point, long base, long total, int logN,
                          int16_t* gt, uint32_t* norms, uint32_t* err, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                     (const uint8_t*)pts, is_signed, n, d, slot_point, base, total, logN, gt,
-                     norms, err);
+  if (total <= 0) return hipSuccess;
+  const uint8_t* p = (const uint8_t*)pts;
+  const dim3 grid((unsigned)((total / 2 + 255) / 256));
+  // the widest load that every row allows
+  if (d % 16 == 0 && (uintptr_t)p % 16 == 0)
+    hipLaunchKernelGGL(k_gather<16>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
+                       total, logN, gt, norms, err);
+  else if (d % 4 == 0 && (uintptr_t)p % 4 == 0)
+    hipLaunchKernelGGL(k_gather<4>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
+                       total, logN, gt, norms, err);
+  else
+    hipLaunchKernelGGL(k_gather<1>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
+                       total, logN, gt, norms, err);
   return hipGetLastError();
 }
 
@@ -2075,16 +2110,8 @@ static hipError_t launch_encode_ntt_t(const G* gt, uint2* dbres, int k0, int nk,
   switch (logN) {
 #define SANNS_CASE(LG)                                                                     \
   case LG:                                                                                 \
-    if (ntt_pairs(ps, LG, L * rows)) {                                                     \
-      if constexpr (LG >= 12)                                                              \
-        hipLaunchKernelGGL((k_encode_ntt<LG, G, 2, true>),                                 \
-                           dim3((unsigned)(L * ((rows + 1) / 2))), dim3(NttShape<LG>::T),  \
-                           NttShape<LG>::lds_bytes_pair, st, gt, dbres, k0, nk, C, d, L,   \
-                           ps, tws);                                                       \
-    } else {                                                                               \
-      ntt_launch<LG>(SANNS_PM(k_encode_ntt, LG, G, 1), (unsigned)(L * rows), st, gt, dbres, \
-                     k0, nk, C, d, L, ps, tws);                                            \
-    }                                                                                      \
+    ntt_launch<LG>(SANNS_PM(k_encode_ntt, LG, G), (unsigned)(L * rows), st, gt, dbres, k0, nk, \
+                   C, d, L, ps, tws);                                                      \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -2133,13 +2160,13 @@ hipError_t launch_slot_ranges(const int64_t* start, const int64_t* len, const in
   return hipGetLastError();
 }
 
-hipError_t launch_gather32(const void* pts, int kind, long n, int d, const uint32_t* norm_shares,
+hipError_t launch_gather32(const uint32_t* pts, long n, int d, const uint32_t* norm_shares,
                            uint32_t t, const int64_t* slot_point, long base, long total,
                            int logN, int32_t* gt, uint32_t* norms, uint32_t* err,
                            hipStream_t st) {
   if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather32, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, pts,
-                     kind, n, d, norm_shares, t, slot_point, base, total, logN, gt, norms, err);
+  hipLaunchKernelGGL(k_gather32, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, pts, n,
+                     d, norm_shares, t, slot_point, base, total, logN, gt, norms, err);
   return hipGetLastError();
 }
 

@@ -119,9 +119,9 @@ hipError_t launch_gather(const void* pts, int is_signed, long n, int d,
 // slot[off[r] + i] = start[r] + i, i < len[r].
 hipError_t launch_slot_ranges(const int64_t* start, const int64_t* len, const int64_t* off,
                               int R, int64_t* slot, long total, hipStream_t st);
-// Gathered chunks: kind 0 / 1 uint8 / int8 points, 2 shares in [0, t) with
-// their norm shares; 32-bit plaintext coefficients.
-hipError_t launch_gather32(const void* pts, int kind, long n, int d, const uint32_t* norm_shares,
+// Gathered chunks of shares in [0, t) with their norm shares: 32-bit plaintext
+// coefficients.
+hipError_t launch_gather32(const uint32_t* pts, long n, int d, const uint32_t* norm_shares,
                            uint32_t t, const int64_t* slot_point, long base, long total,
                            int logN, int32_t* gt, uint32_t* norms, uint32_t* err,
                            hipStream_t st);

@@ -203,15 +203,16 @@ bool call_uses_mfma(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bo
   return mfma_expected_faster(Q, C, d);
 }
 
+// use_digits: the matrix-core schedule may be chosen (its workspace is there).
 void choose_shape(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool regular,
-                  double q_per_chunk, int& qt, int& ct, int& lds) {
+                  double q_per_chunk, int& qt, int& ct, int& lds, bool use_digits = true) {
   lds = 0;
   if (regular && Q >= 2) {
-    if (call_uses_mfma(ctx, Q, C, d, true))
+    if (use_digits && call_uses_mfma(ctx, Q, C, d, true))
       lds = kMfmaSchedule;
     else
       lds = ctx->force_lds > 0 ? ctx->force_lds : kDefaultLdsVariant;
-    if (lds == kMfmaSchedule && !db_has_digits(ctx, d)) lds = kDefaultLdsVariant;
+    if (lds == kMfmaSchedule && !(use_digits && db_has_digits(ctx, d))) lds = kDefaultLdsVariant;
     if (lds != kMfmaSchedule && (int)ctx->p.N % mac_lds_min_n(lds) != 0) lds = 0;
   }
   if (ctx->force_qt > 0) {
@@ -728,12 +729,22 @@ struct CpArgs {
   bool on = false;
 };
 
+// A call's resident tail (sanns_distances_gathered): the work list's rows from
+// `rows0` on are every query against its C chunks, query-major, and run as an
+// all-pairs multiply-accumulate straight on the resident residues.
+struct TailArgs {
+  const uint2* res = nullptr;
+  uint32_t C = 0, rows0 = 0;
+  int qt = 0, ct = 0, lds = 0;
+};
+
 sanns_status enqueue_fused(sanns_ctx* ctx, const sanns_db* db, const uint64_t* ct_in,
                            uint32_t Q, const MaskKey& K, const uint64_t* qids,
                            const uint32_t* dwork, uint32_t M, int qt, int ct, int lds,
                            const void* dtiles, int n_tiles, uint64_t* ct_out,
                            uint32_t* share, uint64_t* qntt, int8_t* qdig, uint64_t* sums,
-                           hipStream_t st, bool profile = false, const CpArgs& cp = CpArgs()) {
+                           hipStream_t st, bool profile = false, const CpArgs& cp = CpArgs(),
+                           const TailArgs& tail = TailArgs()) {
   const uint32_t N = ctx->p.N, L = ctx->p.L, C = db->n_chunks, d = db->d;
   const bool mfma = lds == kMfmaSchedule;
   const uint2* res = (const uint2*)db->mem;
@@ -764,19 +775,28 @@ sanns_status enqueue_fused(sanns_ctx* ctx, const sanns_db* db, const uint64_t* c
                          ctx->tone, share, st));
   HIP_TRY(mark(SANNS_PHASE_MASKS, true));
   HIP_TRY(mark(SANNS_PHASE_MAC, false));
+  auto vector_mac = [&](int qt, int ct, int lds, const uint2* res, const void* tiles, int n_tiles,
+                        uint32_t C, uint64_t* out) -> hipError_t {
+    if (lds > kMacSplit)
+      return launch_mac_split(lds - kMacSplit, (const uint2*)qntt, res, (int)d, (int)L, ctx->logN,
+                              (int)C, ctx->ps, out, st);
+    if (lds > 0)
+      return launch_mac_lds(lds, (const uint2*)qntt, res, (int)Q, (int)d, (int)L, ctx->logN,
+                            (int)C, ctx->ps, out, st);
+    return launch_mac(qt, ct, (const uint2*)qntt, res, tiles, n_tiles, (int)Q, (int)d, (int)L,
+                      ctx->logN, (int)C, ctx->ps, out, st);
+  };
   if (mfma) {
     const int8_t* dig = (const int8_t*)db->mem + (size_t)L * C * d * N * 8 + (size_t)C * N * 4;
     HIP_TRY(launch_mac_mfma(qdig, dig, (int)Q, (int)d, (int)C, (int)L, ctx->logN, ctx->ds,
                             sums, st));
-  } else if (lds > kMacSplit)
-    HIP_TRY(launch_mac_split(lds - kMacSplit, (const uint2*)qntt, res, (int)d, (int)L, ctx->logN,
-                             (int)C, ctx->ps, ct_out, st));
-  else if (lds > 0)
-    HIP_TRY(launch_mac_lds(lds, (const uint2*)qntt, res, (int)Q, (int)d, (int)L, ctx->logN,
-                           (int)C, ctx->ps, ct_out, st));
-  else
-    HIP_TRY(launch_mac(qt, ct, (const uint2*)qntt, res, dtiles, n_tiles, (int)Q, (int)d, (int)L,
-                       ctx->logN, (int)C, ctx->ps, ct_out, st));
+  } else {
+    HIP_TRY(vector_mac(qt, ct, lds, res, dtiles, n_tiles, C, ct_out));
+  }
+  if (tail.C)
+    HIP_TRY(vector_mac(tail.qt, tail.ct, tail.lds, tail.res, nullptr,
+                       (int)(((Q + tail.qt - 1) / tail.qt) * ((tail.C + tail.ct - 1) / tail.ct)),
+                       tail.C, ct_out + (size_t)tail.rows0 * 2 * L * N));
   HIP_TRY(mark(SANNS_PHASE_MAC, true));
   HIP_TRY(mark(SANNS_PHASE_SUMS, false));
   if (mfma)
@@ -856,7 +876,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
                             const uint32_t* work, uint32_t M, int mode, uint64_t* ct_out,
                             uint32_t* server_share, void* workspace, size_t ws_bytes,
                             void* stream, bool noalloc, const uint64_t* pk = nullptr,
-                            uint32_t flood_bits = 0) {
+                            uint32_t flood_bits = 0, TailArgs tail = TailArgs()) {
   if (!ctx || !db || !db->mem || !ct_in || !mask_key || !query_ids || !ct_out ||
       !server_share || !workspace)
     return fail(SANNS_E_INVALID, "null argument");
@@ -879,7 +899,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
   if (M == 0) return SANNS_OK;
   if (work)
     for (uint32_t m = 0; m < M; ++m)
-      if (work[2 * m] >= Q || work[2 * m + 1] >= C)
+      if (work[2 * m] >= Q || work[2 * m + 1] >= C + tail.C)
         return fail(SANNS_E_RANGE, "work[%u] = (%u, %u) outside Q x n_chunks", m, work[2 * m],
                     work[2 * m + 1]);
   const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN &&
@@ -932,21 +952,23 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
 
   int qt, ct, lds;
   double q_per_chunk = Q;
+  const uint32_t listed = tail.C ? tail.rows0 : M;  // rows that the tiles cover
   if (work) {
     std::vector<char> seen(C, 0);
     uint32_t distinct = 0;
-    for (uint32_t m = 0; m < M; ++m)
+    for (uint32_t m = 0; m < listed; ++m)
       if (!seen[work[2 * m + 1]]) {
         seen[work[2 * m + 1]] = 1;
         ++distinct;
       }
-    q_per_chunk = (double)M / (distinct ? distinct : 1);
+    q_per_chunk = (double)listed / (distinct ? distinct : 1);
   }
   if (ctx->force_lds == kMfmaSchedule && !work && Q >= 2 && !db_has_digits(ctx, db->d))
     return fail(SANNS_E_INVALID,
                 "the matrix-core schedule needs SANNS_FLAG_DIGIT_DB, N >= 64 and d <= %d",
                 kMfmaMaxD);
   choose_shape(ctx, Q, C, db->d, work == nullptr, q_per_chunk, qt, ct, lds);
+  if (tail.C) choose_shape(ctx, Q, tail.C, db->d, true, Q, tail.qt, tail.ct, tail.lds, false);
   if (pshape) {
     qt = kPersistTileQ;
     ct = kPersistTileC;
@@ -956,7 +978,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
   const uint32_t* dwork = nullptr;
   int n_tiles;
   if (work) {
-    std::vector<int32_t> tiles = build_tiles(work, M, qt, ct, &n_tiles);
+    std::vector<int32_t> tiles = build_tiles(work, listed, qt, ct, &n_tiles);
     // tiles and the work list go out in one staged copy
     std::vector<char> blob(W.work - W.tiles + (size_t)M * 8);
     std::memcpy(blob.data(), tiles.data(), tiles.size() * 4);
@@ -1005,7 +1027,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
   if (mode == SANNS_MODE_FUSED || (ctx->profiling && !pshape))
     return enqueue_fused(ctx, db, ct_in, Q, K, query_ids, dwork, M, qt, ct, lds, dtiles,
                          n_tiles, ct_out, server_share, qntt, qdig, sums, st, ctx->profiling,
-                         cp);
+                         cp, tail);
 
   // batched and persistent: replay (or capture once) the sequence as a hipGraph
   GraphKey key;
@@ -1097,13 +1119,14 @@ struct GatherLayout {
   size_t db, gt, inner, total, db_bytes;
 };
 
-// Ct: chunks of the resident tail database appended to the call's chunks.
+// Ct: chunks of the resident tail database that follow the call's chunks.
 GatherLayout gather_layout(const sanns_ctx* ctx, uint32_t d, uint32_t Q, uint32_t M,
                            uint32_t Ct) {
-  const size_t N = ctx->p.N, L = ctx->p.L, C = (size_t)M + Ct;
+  const size_t N = ctx->p.N, L = ctx->p.L;
   GatherLayout g;
   g.db = 0;
-  g.db_bytes = L * C * d * N * 8 + C * N * 4;  // residues, then norms
+  // residues of the gathered chunks, then the norms of all chunks
+  g.db_bytes = L * M * d * N * 8 + ((size_t)M + Ct) * N * 4;
   g.gt = align256(g.db_bytes);
   g.inner = g.gt + align256((size_t)gather_batch(d, (uint32_t)N, M) * d * N * 4);
   g.total = g.inner + ws_layout(ctx, d, Q, M + Q * Ct, false).total;
@@ -1151,7 +1174,7 @@ extern "C" sanns_status sanns_distances_gathered(
   for (uint32_t m = 0; m < M; ++m)
     if (row_query[m] >= Q)
       return fail(SANNS_E_RANGE, "row_query[%u] = %u outside [0, Q)", m, row_query[m]);
-  const uint32_t Ct = tail ? tail->n_chunks : 0, C = M + Ct;
+  const uint32_t Ct = tail ? tail->n_chunks : 0;
   const uint64_t rows = (uint64_t)M + (uint64_t)Q * Ct;
   if (rows > 0x7FFFFFFFull) return fail(SANNS_E_INVALID, "too many output rows");
   const GatherLayout G = gather_layout(ctx, d, Q, M, Ct);
@@ -1162,34 +1185,44 @@ extern "C" sanns_status sanns_distances_gathered(
   const uint32_t N = ctx->p.N, L = ctx->p.L;
   char* ws = (char*)workspace;
   uint2* res = (uint2*)(ws + G.db);
-  uint32_t* norms = (uint32_t*)(ws + G.db + (size_t)L * C * d * N * 8);
+  uint32_t* norms = (uint32_t*)(ws + G.db + (size_t)L * M * d * N * 8);
   int32_t* gt = (int32_t*)(ws + G.gt);
-  const uint32_t batch = gather_batch(d, N, M);
-  const int kind = dtype == SANNS_SHARE32 ? 2 : (dtype == SANNS_I8 ? 1 : 0);
+  // points as 16-bit plaintexts, shares as 32-bit ones; the buffer holds a
+  // batch of the latter
+  const bool shares = dtype == SANNS_SHARE32;
+  const uint32_t batch = (shares ? 1 : 2) * gather_batch(d, N, M);
   for (uint32_t k0 = 0; k0 < M; k0 += batch) {
     const uint32_t nk = std::min(batch, M - k0);
-    HIP_TRY(launch_gather32(points, kind, (long)n, (int)d, norm_shares, (uint32_t)ctx->p.t,
-                            slot_point, (long)k0 * N, (long)nk * N, ctx->logN, gt, norms,
-                            ctx->d_err, st));
-    HIP_TRY(launch_encode_ntt32(gt, res, (int)k0, (int)nk, (int)C, (int)d, ctx->logN, (int)L,
-                                ctx->ps, ctx->tws, st));
+    if (shares) {
+      HIP_TRY(launch_gather32((const uint32_t*)points, (long)n, (int)d, norm_shares,
+                              (uint32_t)ctx->p.t, slot_point, (long)k0 * N, (long)nk * N,
+                              ctx->logN, gt, norms, ctx->d_err, st));
+      HIP_TRY(launch_encode_ntt32(gt, res, (int)k0, (int)nk, (int)M, (int)d, ctx->logN, (int)L,
+                                  ctx->ps, ctx->tws, st));
+    } else {
+      HIP_TRY(launch_gather(points, dtype == SANNS_I8, (long)n, (int)d, slot_point, (long)k0 * N,
+                            (long)nk * N, ctx->logN, (int16_t*)gt, norms, ctx->d_err, st));
+      HIP_TRY(launch_encode_ntt((const int16_t*)gt, res, (int)k0, (int)nk, (int)M, (int)d,
+                                ctx->logN, (int)L, ctx->ps, ctx->tws, st));
+    }
   }
   if (Ct) {
-    // the tail's resident NTT form and norms follow the gathered chunks
-    const size_t plane = (size_t)d * N;  // uint2 words of one chunk and limb
-    const uint2* tres = (const uint2*)tail->mem;
-    for (uint32_t l = 0; l < L; ++l)
-      HIP_TRY(hipMemcpyAsync(res + ((size_t)l * C + M) * plane, tres + (size_t)l * Ct * plane,
-                             (size_t)Ct * plane * sizeof(uint2), hipMemcpyDeviceToDevice, st));
-    const uint32_t* tnorms = (const uint32_t*)((const char*)tail->mem + (size_t)L * Ct * plane * 8);
+    // the tail's norms follow the gathered chunks'; its residues are read where
+    // they are
+    const uint32_t* tnorms =
+        (const uint32_t*)((const char*)tail->mem + (size_t)L * Ct * d * N * 8);
     HIP_TRY(hipMemcpyAsync(norms + (size_t)M * N, tnorms, (size_t)Ct * N * 4,
                            hipMemcpyDeviceToDevice, st));
   }
   sanns_db tmp;
   tmp.mem = res;
   tmp.bytes = G.db_bytes;
-  tmp.n_chunks = C;
+  tmp.n_chunks = M;
   tmp.d = d;
+  TailArgs T;
+  T.res = Ct ? (const uint2*)tail->mem : nullptr;
+  T.C = Ct;
+  T.rows0 = M;
   std::vector<uint32_t> work(2 * (size_t)rows);
   for (uint32_t m = 0; m < M; ++m) {
     work[2 * m] = row_query[m];
@@ -1203,7 +1236,7 @@ extern "C" sanns_status sanns_distances_gathered(
     }
   return distances_impl(ctx, &tmp, ct_in, Q, mask_key, query_ids, work.data(), (uint32_t)rows,
                         SANNS_MODE_FUSED, ct_out, server_share, ws + G.inner, G.total - G.inner,
-                        stream, false);
+                        stream, false, nullptr, 0, T);
 }
 
 // ---------------------------------------------------------------------------
