@@ -79,7 +79,10 @@ __device__ __forceinline__ uint32_t gather_byte(uint64_t y0, uint64_t y1, uint64
 // halves), stages the words in LDS, and writes each slot's 7 digit rows of
 // Dp bytes (16 bytes per store, zero digits past coordinate d; two threads
 // share a slot's 16-coordinate group, one for digits 0-3, one for 4-6).  The
-// query side is read and written with nontemporal hints: it is touched once.
+// query side is read and written with nontemporal hints: it is touched once, in
+// whole lines.  The database's rows (7 Dp + 16 bytes) start anywhere in a line,
+// so its stores are plain ones, which the L2 merges into whole lines: 0.41 ->
+// 0.29 ms for 25 chunks of 128 coordinates at N = 8192, L = 3.
 // LDS word (i, pp) sits at i (S + 1) + pp + i / 16: the extra word per 16
 // coordinates puts the 16-coordinate groups that the lanes of one read
 // instruction take on different banks (without it, eight of them share one).
@@ -147,7 +150,11 @@ k_to_digits(const void* __restrict__ src, int8_t* __restrict__ dst, int n_ent, i
       v.y = gather_byte(y[4], y[5], y[6], y[7], a);
       v.z = gather_byte(y[8], y[9], y[10], y[11], a);
       v.w = gather_byte(y[12], y[13], y[14], y[15], a);
-      __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(row + a * Dp + 16 * cg));
+      v4u* dst = reinterpret_cast<v4u*>(row + a * Dp + 16 * cg);
+      if (DB)
+        *dst = v;
+      else
+        __builtin_nontemporal_store(v, dst);
     }
     if (DB && cg == 0 && hf == 0) *reinterpret_cast<uint4*>(row + 7 * Dp) = make_uint4(0, 0, 0, 0);
   }
