@@ -89,6 +89,7 @@ hipError_t launch_persistent(int shape, const PersistArgs& A, const PrimeSet& ps
 constexpr int kMfmaSchedule = 81;  // schedule id of sanns_set_schedule
 constexpr int kMfmaMaxD = 128;     // largest d (two MFMA steps of 64 coordinates)
 bool mfma_supported(int logN, int d);
+int mfma_rows_per_tile(int Q);  // rows (two per query) of a workgroup's tile: 16, 32 or 64
 int mfma_padded_d(int d);   // d rounded up to 32: database digit rows, contraction
 int mfma_query_d(int d);    // d rounded up to 64: query digit rows
 int mfma_db_stride(int d);  // bytes per (limb, slot, chunk) of the database digits
@@ -101,7 +102,8 @@ hipError_t launch_query_digits(const uint64_t* qntt, int8_t* qd, int Q, int d, i
 hipError_t launch_db_digits(const uint2* dbres, int8_t* dbd, int C, int d, int L, int logN,
                             hipStream_t st);
 // All-pairs sums into the slot-major buffer `sums` ([L][N][Rp][Cp] uint64
-// below 2^58, Rp = 2Q and Cp = C rounded up to 64; mfma_sums_bytes).
+// below 2^58, Rp = 2Q rounded up to whole row tiles and Cp = C to 64;
+// mfma_sums_bytes).
 size_t mfma_sums_bytes(int Q, int C, int L, int logN);
 hipError_t launch_mac_mfma(const int8_t* qd, const int8_t* dbd, int Q, int d, int C, int L,
                            int logN, const DigitSet& ds, uint64_t* sums, hipStream_t st);

@@ -27,7 +27,7 @@
 //   database digits [L][N][C][Sk] int8       Sk = 7 Dp + 16: digit rows, then
 //                                            16 bytes of padding (LDS banks)
 //   slot-major sums [L][N][Rp][Cp] uint64 below 2^58, congruent mod q_l (R and
-//                   C padded to whole tiles of 64 rows and 64 chunks)
+//                   C padded to whole tiles of 16, 32 or 64 rows and 64 chunks)
 // Fragment of one lane (row or column m = lane % 16, group g = lane / 16) at
 // step s: the 16 bytes of one digit row at coordinates 64s + 16g .. + 15, or
 // in a 32-coordinate step the 8 bytes at 64s + 8g .. + 7.
@@ -42,7 +42,16 @@ namespace sanns {
 typedef int v4i __attribute__((ext_vector_type(4)));
 
 constexpr uint64_t kDigitBias = 0x0080808080808080ull;  // 128 in each of bytes 0..6
-constexpr int kMfmaRows = 64;    // rows per workgroup: 4 waves x 16
+// Rows per workgroup, 16 for each of its waves: 64, and for batches of at most
+// 16 or 8 queries 32 or 16.  A few rows leave the kernel waiting for the
+// database digits, which every row tile streams once whatever its height, so
+// padding 18 rows to 64 cost twice the products and stores for nothing: 9 queries
+// of 96 coordinates against 123 chunks take 0.66 ms in 32 rows (the vector
+// schedule 1.16 ms).
+__host__ __device__ constexpr int mfma_row_tile(int R) { return R <= 16 ? 16 : R <= 32 ? 32 : 64; }
+__host__ __device__ constexpr int mfma_padded_rows(int R) {
+  return (R + mfma_row_tile(R) - 1) / mfma_row_tile(R) * mfma_row_tile(R);
+}
 constexpr int kMfmaChunks = 64;  // chunks per workgroup: 4 stages of one 16-chunk MFMA column tile
 constexpr int kMfmaSlots = 8;    // consecutive slots per workgroup
 constexpr int kDigitGroup = 32;  // slots per group of the query NTT form (form 2)
@@ -244,8 +253,8 @@ __device__ __forceinline__ v4i mfma_digits(typename StepFrag<W32>::T a,
     return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
 }
 
-// One workgroup: 64 rows x 64 chunks of kMfmaSlots consecutive slots of one
-// limb.  Wave w owns rows 16w .. 16w + 15 of the tile; its query fragments
+// One workgroup: 16 RW rows (RW waves; 64 rows below) x 64 chunks of kMfmaSlots
+// consecutive slots of one limb.  Wave w owns rows 16w .. 16w + 15 of the tile; its query fragments
 // come straight from global memory into registers and serve the four
 // 16-chunk column tiles of a slot.  The database digits are staged in LDS by
 // DMA (global_load_lds) one column tile (stage) at a time, double-buffered
@@ -265,8 +274,8 @@ __device__ __forceinline__ v4i mfma_digits(typename StepFrag<W32>::T a,
 // around each barrier keep them behind it.  Workgroups are numbered so that
 // the tiles of one slot range run back to back on one XCD, which shares the
 // operands in its L2.
-template <int DP, bool PM>
-__global__ void __launch_bounds__(256, 3)
+template <int DP, bool PM, int RW>
+__global__ void __launch_bounds__(64 * RW, 3)
 k_mac_mfma(const int8_t* __restrict__ qd, const int8_t* __restrict__ dbd, int R, int C, int L,
              int logN, int n_items, DigitSet ds, uint64_t* __restrict__ sums) {
   constexpr int Dp = DP, Sk = 7 * Dp + 16, Dq = (Dp + 63) / 64 * 64;
@@ -276,24 +285,25 @@ k_mac_mfma(const int8_t* __restrict__ qd, const int8_t* __restrict__ dbd, int R,
   typedef typename StepFrag<W1>::T F1;
   constexpr int H = 16;                 // chunks per stage
   constexpr int BU = H * Sk / 16;       // 16-byte units of one stage
-  constexpr int BR = (BU + 255) / 256;  // DMA rounds of the 256 threads
-  static_assert(BR * 256 * 16 + (kMfmaChunks - H) * Sk <= (int)kMfmaDbSlack,
+  constexpr int NT = 64 * RW;           // threads
+  constexpr int BR = (BU + NT - 1) / NT;  // DMA rounds of the workgroup
+  static_assert(BR * NT * 16 + (kMfmaChunks - H) * Sk <= (int)kMfmaDbSlack,
                 "a stage's DMA stays inside the digit region's slack");
   static_assert(!PM || Dp <= 128, "the bounds of the short fold hold for Dp <= 128");
-  __shared__ uint4 sb0[BR * 256], sb1[BR * 256];
+  __shared__ uint4 sb0[BR * NT], sb1[BR * NT];
   const int N = 1 << logN;
   const int per_xcd = (n_items + 7) >> 3;
   const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (lin >= n_items) return;
-  const int nrt = (R + kMfmaRows - 1) / kMfmaRows, nct = (C + kMfmaChunks - 1) / kMfmaChunks;
-  const int Rp = nrt * kMfmaRows, Cp = nct * kMfmaChunks;
+  const int nrt = (R + 16 * RW - 1) / (16 * RW), nct = (C + kMfmaChunks - 1) / kMfmaChunks;
+  const int Rp = nrt * 16 * RW, Cp = nct * kMfmaChunks;
   const int tile = lin % (nrt * nct), sg = lin / (nrt * nct);
   const int rt = tile % nrt, ctile = tile / nrt;
   const int l = sg % L, p0 = (sg / L) * kMfmaSlots;
   const int k0 = ctile * kMfmaChunks;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int m16 = lane & 15, g = lane >> 4;
-  const int wrow0 = rt * kMfmaRows + 16 * w;
+  const int wrow0 = rt * 16 * RW + 16 * w;
   const int arow = wrow0 + m16 < R ? wrow0 + m16 : R - 1;
   const DigitConst& D = ds.c[l];
   // opaque 1, 2^8, 2^16, 2^24: the fold's terms become 64-bit multiply-adds
@@ -305,8 +315,8 @@ k_mac_mfma(const int8_t* __restrict__ qd, const int8_t* __restrict__ dbd, int R,
 #pragma unroll
     for (int m = 0; m < BR; ++m)
       __builtin_amdgcn_global_load_lds(
-          (const void*)(src + tid + 256 * m),
-          (__attribute__((address_space(3))) void*)(buf + 256 * m + 64 * w), 16, 0, 0);
+          (const void*)(src + tid + NT * m),
+          (__attribute__((address_space(3))) void*)(buf + NT * m + 64 * w), 16, 0, 0);
   };
   auto load_a = [&](int p, int ks, auto (&af)[7]) {
     typedef typename std::remove_reference<decltype(af[0])>::type F;
@@ -434,7 +444,7 @@ k_sums_to_ct(const uint64_t* __restrict__ sums, uint64_t* __restrict__ ct, int R
   const int pg = b % ng, l = b / ng;
   const int p0 = pg * 64, k0 = kg * 32;
   const int tid = threadIdx.x;
-  const int Rp = (R + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
+  const int Rp = mfma_padded_rows(R);
   const int Cp = (C + kMfmaChunks - 1) / kMfmaChunks * kMfmaChunks;
   // two consecutive chunks of a slot per 16-byte load (Cp is a multiple of 64)
   typedef uint64_t u64x2v __attribute__((ext_vector_type(2)));
@@ -488,10 +498,11 @@ k_sums_to_ct(const uint64_t* __restrict__ sums, uint64_t* __restrict__ ct, int R
 // launchers
 // --------------------------------------------------------------------------
 
+int mfma_rows_per_tile(int Q) { return mfma_row_tile(2 * Q); }
 int mfma_padded_d(int d) { return (d + 31) / 32 * 32; }
 int mfma_query_d(int d) { return (d + 63) / 64 * 64; }
 size_t mfma_sums_bytes(int Q, int C, int L, int logN) {
-  const size_t Rp = (2 * (size_t)Q + kMfmaRows - 1) / kMfmaRows * kMfmaRows;
+  const size_t Rp = mfma_padded_rows(2 * Q);
   const size_t Cp = ((size_t)C + kMfmaChunks - 1) / kMfmaChunks * kMfmaChunks;
   return (size_t)L * ((size_t)1 << logN) * Rp * Cp * sizeof(uint64_t);
 }
@@ -527,22 +538,22 @@ hipError_t launch_db_digits(const uint2* dbres, int8_t* dbd, int C, int d, int L
   return hipGetLastError();
 }
 
-template <int DP>
+template <int DP, int RW>
 static void launch_mac_mfma_t(const int8_t* qd, const int8_t* dbd, int R, int C, int L, int logN,
                               const DigitSet& ds, uint64_t* sums, hipStream_t st) {
   const int N = 1 << logN;
-  const long n_items = (long)L * (N / kMfmaSlots) * ((R + kMfmaRows - 1) / kMfmaRows) *
+  const long n_items = (long)L * (N / kMfmaSlots) * (mfma_padded_rows(R) / (16 * RW)) *
                        ((C + kMfmaChunks - 1) / kMfmaChunks);
   const long per_xcd = (n_items + 7) >> 3;
   // the short fold when every prime is 2^54 - delta with a small delta
   bool pm = true;
   for (int l = 0; l < L; ++l) pm = pm && ds.c[l].delta != 0;
   if (pm)
-    hipLaunchKernelGGL((k_mac_mfma<DP, true>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
-                       qd, dbd, R, C, L, logN, (int)n_items, ds, sums);
+    hipLaunchKernelGGL((k_mac_mfma<DP, true, RW>), dim3((unsigned)(per_xcd * 8)), dim3(64 * RW),
+                       0, st, qd, dbd, R, C, L, logN, (int)n_items, ds, sums);
   else
-    hipLaunchKernelGGL((k_mac_mfma<DP, false>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, st,
-                       qd, dbd, R, C, L, logN, (int)n_items, ds, sums);
+    hipLaunchKernelGGL((k_mac_mfma<DP, false, RW>), dim3((unsigned)(per_xcd * 8)), dim3(64 * RW),
+                       0, st, qd, dbd, R, C, L, logN, (int)n_items, ds, sums);
 }
 
 hipError_t launch_mac_mfma(const int8_t* qd, const int8_t* dbd, int Q, int d, int C, int L,
@@ -551,10 +562,20 @@ hipError_t launch_mac_mfma(const int8_t* qd, const int8_t* dbd, int Q, int d, in
   if (Q <= 0 || C <= 0) return hipSuccess;
   const int R = 2 * Q;
   switch (mfma_padded_d(d)) {
-    case 32: launch_mac_mfma_t<32>(qd, dbd, R, C, L, logN, ds, sums, st); break;
-    case 64: launch_mac_mfma_t<64>(qd, dbd, R, C, L, logN, ds, sums, st); break;
-    case 96: launch_mac_mfma_t<96>(qd, dbd, R, C, L, logN, ds, sums, st); break;
-    case 128: launch_mac_mfma_t<128>(qd, dbd, R, C, L, logN, ds, sums, st); break;
+#define SANNS_MFMA_CASE(DP)                                                             \
+  case DP:                                                                              \
+    if (mfma_row_tile(R) == 16)                                                         \
+      launch_mac_mfma_t<DP, 1>(qd, dbd, R, C, L, logN, ds, sums, st);                   \
+    else if (mfma_row_tile(R) == 32)                                                    \
+      launch_mac_mfma_t<DP, 2>(qd, dbd, R, C, L, logN, ds, sums, st);                   \
+    else                                                                                \
+      launch_mac_mfma_t<DP, 4>(qd, dbd, R, C, L, logN, ds, sums, st);                   \
+    break;
+    SANNS_MFMA_CASE(32)
+    SANNS_MFMA_CASE(64)
+    SANNS_MFMA_CASE(96)
+    SANNS_MFMA_CASE(128)
+#undef SANNS_MFMA_CASE
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

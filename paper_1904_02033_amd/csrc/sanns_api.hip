@@ -185,8 +185,28 @@ bool db_has_digits(const sanns_ctx* ctx, uint32_t d) {
 // multiply-accumulate 8.6 ms (scales with Q C d); the matrix-core path's
 // digit transpose 1.35 ms (Q Dq), MFMA tiles 2.4 ms (64-row x 64-chunk tiles
 // x Dp, 4 of them) and sums transpose 1.25 ms (Q C).
-bool mfma_expected_faster(uint32_t Q, uint32_t C, uint32_t d) {
+// With at most 16 queries (row tiles of 16 or 32, `small`) the tiles cost what
+// streaming the digits costs, 2.7 us per coordinate and 64-chunk tile, and 90 us
+// more with 32 rows; the vector schedule works in tiles of 4 queries x 16 chunks
+// and takes at least the time to stream its residues (0.75 ms), and its masks
+// are a launch of their own (0.61 ms).  Both sides measured at N = 8192, L = 3
+// (whole calls, vector / matrix-core): 123 chunks, d = 96, Q = 2: 0.67 / 0.76
+// ms, Q = 5: 1.18 / 1.01, Q = 9: 1.77 / 1.40, Q = 16: 2.53 / 2.07; d = 128, Q =
+// 3: 0.99 / 1.00, Q = 8: 1.70 / 1.50; d = 32, Q = 9: 0.89 / 0.94; 37 chunks, d =
+// 128, Q = 8: 0.72 / 0.82, Q = 16: 1.38 / 1.38; 13 chunks, d = 96, Q = 16: 0.64
+// / 1.02.
+bool mfma_expected_faster(uint32_t Q, uint32_t C, uint32_t d, bool small) {
   const double Dp = mfma_padded_d((int)d), Dq = mfma_query_d((int)d);
+  const int rows = mfma_rows_per_tile((int)Q);
+  if (small && rows < 64) {
+    const double vtile = 8.6 * ((Q + 3) / 4 * 4) * ((C + 15) / 16 * 16) * (double)d / (64.0 * 128 * 128);
+    const double vector = std::max(vtile, 0.75 * C * (double)d / (123.0 * 128)) +
+                          0.61 * (double)Q * C / (64.0 * 123);
+    const double tile = 0.0027 * Dp + (rows == 32 ? 0.09 : 0.0);
+    return 1.13 * Q * Dq / (64.0 * 128) + ((C + 63) / 64) * tile +
+               1.37 * (double)Q * C / (64.0 * 123) <
+           vector;
+  }
   const double valu = 8.6 * (double)Q * C * d / (64.0 * 123 * 128);
   const double tiles = (double)((2 * Q + 63) / 64) * ((C + 63) / 64);
   const double mfma = 1.35 * Q * Dq / (64.0 * 128) + 2.4 * tiles * Dp / (4.0 * 128) +
@@ -196,23 +216,27 @@ bool mfma_expected_faster(uint32_t Q, uint32_t C, uint32_t d) {
 
 // Whether an all-pairs (or not) call of Q queries against C chunks runs the
 // matrix-core schedule: forced by sanns_set_schedule, or chosen by default on
-// a digit database when the cost model predicts it faster.
-bool call_uses_mfma(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool all_pairs) {
+// a digit database when the cost model predicts it faster.  small = false (calls
+// on the library's own scratch, sanns_distances_noalloc): the choice as if every
+// batch were padded to 64 rows, which leaves small batches, and with them the
+// workspace that the scratch has to hold, to the vector schedule.
+bool call_uses_mfma(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool all_pairs,
+                    bool small = true) {
   if (!all_pairs || Q < 2 || !db_has_digits(ctx, d)) return false;
   if (ctx->force_lds > 0) return ctx->force_lds == kMfmaSchedule;
-  return mfma_expected_faster(Q, C, d);
+  return mfma_expected_faster(Q, C, d, small);
 }
 
-// use_digits: the matrix-core schedule may be chosen (its workspace is there).
+// mfma: an all-pairs call runs the matrix-core schedule (call_uses_mfma).
 void choose_shape(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool regular,
-                  double q_per_chunk, int& qt, int& ct, int& lds, bool use_digits = true) {
+                  double q_per_chunk, int& qt, int& ct, int& lds, bool mfma) {
   lds = 0;
   if (regular && Q >= 2) {
-    if (use_digits && call_uses_mfma(ctx, Q, C, d, true))
+    if (mfma)
       lds = kMfmaSchedule;
     else
       lds = ctx->force_lds > 0 ? ctx->force_lds : kDefaultLdsVariant;
-    if (lds == kMfmaSchedule && !(use_digits && db_has_digits(ctx, d))) lds = kDefaultLdsVariant;
+    if (lds == kMfmaSchedule && !mfma) lds = kDefaultLdsVariant;
     if (lds != kMfmaSchedule && (int)ctx->p.N % mac_lds_min_n(lds) != 0) lds = 0;
   }
   if (ctx->force_qt > 0) {
@@ -903,7 +927,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
         return fail(SANNS_E_RANGE, "work[%u] = (%u, %u) outside Q x n_chunks", m, work[2 * m],
                     work[2 * m + 1]);
   const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN &&
-                    call_uses_mfma(ctx, Q, C, db->d, work == nullptr);
+                    call_uses_mfma(ctx, Q, C, db->d, work == nullptr, !noalloc);
   const bool cp_on = pk != nullptr;
   if (cp_on && mode != SANNS_MODE_FUSED && mode != SANNS_MODE_BATCHED)
     return fail(SANNS_E_INVALID, "the circuit-private form runs in SANNS_MODE_FUSED or "
@@ -967,7 +991,7 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
     return fail(SANNS_E_INVALID,
                 "the matrix-core schedule needs SANNS_FLAG_DIGIT_DB, N >= 64 and d <= %d",
                 kMfmaMaxD);
-  choose_shape(ctx, Q, C, db->d, work == nullptr, q_per_chunk, qt, ct, lds);
+  choose_shape(ctx, Q, C, db->d, work == nullptr, q_per_chunk, qt, ct, lds, mfma);
   if (tail.C) choose_shape(ctx, Q, tail.C, db->d, true, Q, tail.qt, tail.ct, tail.lds, false);
   if (pshape) {
     qt = kPersistTileQ;
@@ -1333,7 +1357,8 @@ extern "C" sanns_status sanns_distances_noalloc(sanns_ctx* ctx, const sanns_db* 
   if (!ctx->scratch) return fail(SANNS_E_DEVICE, "no scratch address for device %d", ctx->device);
   const uint64_t M = (uint64_t)Q * db->n_chunks;
   if (M > 0xFFFFFFFFull) return fail(SANNS_E_INVALID, "Q * n_chunks overflows");
-  const size_t need = sanns_distances_workspace(ctx, db, Q, (uint32_t)M, SANNS_MODE_FUSED);
+  const bool mfma = Q > 0 && call_uses_mfma(ctx, Q, db->n_chunks, db->d, true, false);
+  const size_t need = ws_layout(ctx, db->d, Q, (uint32_t)M, mfma).total;
   if (need > (size_t)SANNS_NOALLOC_SCRATCH_BYTES)
     return fail(SANNS_E_WORKSPACE,
                 "the call needs %zu bytes of scratch, more than the %u bytes the library holds "
