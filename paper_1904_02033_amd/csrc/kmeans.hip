@@ -259,7 +259,96 @@ k_km_accum2(const int8_t* __restrict__ X, long n, int d, const int32_t* __restri
   if (i == 0) atomicAdd((unsigned long long*)&counts[a], 1ull);
 }
 
-// The same for n beyond that bound: thread per (point, coordinate), two's
+// The same with the adds gathered in LDS first: a workgroup takes one part of
+// the points and PAIRS coordinate pairs, adds into its own table of every
+// cluster (k PAIRS words, then k counts that the workgroups of the first pairs
+// keep), and then adds the table to the global sums.  Few atomics leave the
+// workgroup, and clusters that many points share do not queue in the L2.
+constexpr int kKmAccThreads = 1024;
+template <int PAIRS>
+__global__ void __launch_bounds__(kKmAccThreads)
+k_km_accum_lds(const int8_t* __restrict__ X, long n, int d, const int32_t* __restrict__ assign,
+               int k, int slices, long part_len, uint64_t* __restrict__ sums,
+               uint64_t* __restrict__ counts) {
+  extern __shared__ uint64_t tab[];
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(tab + (size_t)k * PAIRS);
+  const int h = (d + 1) / 2, tid = threadIdx.x;
+  const int slice = blockIdx.x % slices;
+  const long p0 = (blockIdx.x / slices) * part_len;
+  const long p1 = p0 + part_len < n ? p0 + part_len : n;
+  for (int u = tid; u < k * PAIRS; u += kKmAccThreads) tab[u] = 0;
+  for (int u = tid; u < k; u += kKmAccThreads) cnt[u] = 0;
+  __syncthreads();
+  const int j = tid % PAIRS, i = slice * PAIRS + j;
+  if (i < h) {
+    constexpr int U = 8, STEP = kKmAccThreads / PAIRS;  // points in flight per thread
+    const bool two = 2 * i + 1 < d;
+    for (long pt = p0 + tid / PAIRS; pt < p1; pt += U * STEP) {
+      int a[U];
+      uint64_t v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const long q = pt + u * STEP < p1 ? pt + u * STEP : pt;
+        const int8_t* x = X + q * d + 2 * i;
+        a[u] = pt + u * STEP < p1 ? assign[q] : -1;
+        v[u] = (uint64_t)(uint32_t)(x[0] + 128) |
+               (uint64_t)(two ? (uint32_t)(x[two] + 128) : 0u) << 32;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (a[u] < 0 || a[u] >= k) continue;
+        atomicAdd((unsigned long long*)&tab[a[u] * PAIRS + j], (unsigned long long)v[u]);
+        if (i == 0) atomicAdd(&cnt[a[u]], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (int u = tid; u < k * PAIRS; u += kKmAccThreads) {
+    const int a = u / PAIRS, ii = slice * PAIRS + u % PAIRS;
+    if (tab[u]) atomicAdd((unsigned long long*)&sums[(size_t)a * h + ii], (unsigned long long)tab[u]);
+  }
+  if (slice == 0)
+    for (int a = tid; a < k; a += kKmAccThreads)
+      if (cnt[a]) atomicAdd((unsigned long long*)&counts[a], (unsigned long long)cnt[a]);
+}
+
+// Parts of the points for that form, 0 where it is not the one to take: the
+// tables must fit a CU's LDS (k up to 7,680 with two pairs each), a part needs
+// points enough that few adds leave it (n >= 64 k, four for each table entry and
+// 16 parts), and with fewer than 32 workgroups the chip would idle.  Whole
+// updates, global adds / LDS tables: n = 200,000, d = 96, k = 30: 670 / 29 us, k =
+// 300: 198 / 35, k = 2,000: 81 / 52; n = 1,000,000, k = 1,000: 446 / 106; below
+// the line n = 100,000, d = 128, k = 2,500: 60 / 65 and n = 200,000, k = 5,000:
+// 78 / 90.
+static int km_accum_parts(long n, int d, int k, int* pairs) {
+  constexpr size_t kLds = 150 * 1024;
+  *pairs = 0;
+  for (int p : {8, 4, 2})
+    if (!*pairs && (size_t)k * (8 * p + 4) <= kLds) *pairs = p;
+  if (!*pairs || n < 64l * k) return 0;
+  const int slices = ((d + 1) / 2 + *pairs - 1) / *pairs;
+  const long most = slices >= 256 ? 1 : 256 / slices;
+  const long parts = n / (4l * k) < most ? n / (4l * k) : most;
+  return parts * slices < 32 ? 0 : (int)parts;
+}
+
+template <int PAIRS>
+static bool launch_km_accum_lds(const int8_t* X, long n, int d, const int32_t* assign, int k,
+                                int parts, uint64_t* sums, uint64_t* counts, hipStream_t st) {
+  const int slices = ((d + 1) / 2 + PAIRS - 1) / PAIRS;
+  const size_t lds = (size_t)k * (8 * PAIRS + 4);
+  if (lds > 64 * 1024 &&
+      hipFuncSetAttribute((const void*)k_km_accum_lds<PAIRS>,
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+    (void)hipGetLastError();  // the other form takes the call
+    return false;
+  }
+  hipLaunchKernelGGL(k_km_accum_lds<PAIRS>, dim3((unsigned)(slices * parts)), dim3(kKmAccThreads), lds, st,
+                     X, n, d, assign, k, slices, (n + parts - 1) / parts, sums, counts);
+  return true;
+}
+
+// The sums for n where a pair could carry: thread per (point, coordinate), two's
 // complement 64-bit sums.
 __global__ void __launch_bounds__(256)
 k_km_accum(const int8_t* __restrict__ X, long n, int d, const int32_t* __restrict__ assign,
@@ -369,7 +458,14 @@ hipError_t launch_km_update(const int8_t* X, long n, int d, const int32_t* assig
   hipLaunchKernelGGL(k_km_zero, dim3((unsigned)((zc + 255) / 256)), dim3(256), 0, st, sums, zc);
   const int paired = n < (1l << 32) / 255;
   const long t = n * (paired ? (d + 1) / 2 : d);
-  if (t > 0) {
+  int pairs = 0;
+  const int parts = paired ? km_accum_parts(n, d, k, &pairs) : 0;
+  const bool done =
+      parts > 0 &&
+      (pairs == 8   ? launch_km_accum_lds<8>(X, n, d, assign, k, parts, sums, counts, st)
+       : pairs == 4 ? launch_km_accum_lds<4>(X, n, d, assign, k, parts, sums, counts, st)
+                    : launch_km_accum_lds<2>(X, n, d, assign, k, parts, sums, counts, st));
+  if (!done && t > 0) {
     if (paired)
       hipLaunchKernelGGL(k_km_accum2, dim3((unsigned)((t + 255) / 256)), dim3(256), 0, st, X, n,
                          d, assign, k, sums, counts);

@@ -184,6 +184,30 @@ def test_kmeans_tile_edges(mods, n, d, k):
     assert (Cd.cpu().numpy() == obal.update(X, want, C)).all()
 
 
+# sums gathered in LDS tables of 8, 4 and 2 coordinate pairs, at both sides of
+# each table's largest k and of n = 64 k; d odd and one slice short
+@pytest.mark.parametrize("k", [1, 40, 2258, 2260, 4265, 4267, 7679, 7682])
+@pytest.mark.parametrize("extra", [-1, 0, 777])
+def test_kmeans_update_tables(mods, k, extra):
+    nat, _ = mods
+    n, d = max(64 * k, 20000) + extra, 33
+    g = torch.Generator(device="cuda").manual_seed(k + extra)
+    X = torch.randint(-128, 128, (n, d), dtype=torch.int8, device="cuda", generator=g)
+    a = torch.randint(-1, k + 1, (n,), dtype=torch.int32, device="cuda", generator=g)
+    C = torch.full((k, d), 7, dtype=torch.int32, device="cuda")
+    cnt = torch.empty(k, dtype=torch.int64, device="cuda")
+    ws = torch.empty(nat.sanns_kmeans_workspace(k, d), dtype=torch.uint8, device="cuda")
+    nat.sanns_kmeans_update(X.data_ptr(), n, d, a.data_ptr(), k, C.data_ptr(), cnt.data_ptr(),
+                            ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    x, lab = X.cpu().numpy().astype(np.int64), a.cpu().numpy()
+    real = (lab >= 0) & (lab < k)
+    c = np.bincount(lab[real], minlength=k)
+    s = np.stack([np.bincount(lab[real], weights=x[real, i], minlength=k) for i in range(d)], 1)
+    want = np.where(c[:, None] > 0, (512 * s.astype(np.int64) + c[:, None]) //
+                    np.maximum(2 * c[:, None], 1), 7)
+    assert (cnt.cpu().numpy() == c).all() and (C.cpu().numpy() == want).all()
+
+
 @pytest.mark.parametrize("n", [(1 << 32) // 255 - 1, (1 << 32) // 255 + 1])
 def test_kmeans_update_many_points(mods, n):
     """Both forms of the sums: two coordinates per add, and one where their
