@@ -71,8 +71,11 @@ k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restri
 // indices beyond 22 bits are taken in blocks, whose winners are compared in 64
 // bits.  At n = 200,000, d = 96, k = 2,000: 1.18 ms by 4-way dot products on the
 // vector units, 0.15 ms here.
+// (At least two waves per SIMD: with all 512 registers of one the compiler puts
+// the sums in the accumulation half and copies each out, 32 more instructions
+// for 64 candidates.)
 template <int DW>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, DW <= 24 ? 4 : DW <= 40 ? 3 : 2)
 k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
             const int32_t* __restrict__ packed, const int64_t* __restrict__ cnorm, int k,
             const int32_t* __restrict__ prev, int32_t* __restrict__ assign,
