@@ -44,8 +44,7 @@ __device__ __forceinline__ uint64_t mulmod(uint64_t a, uint64_t b, const Prime& 
 // forward / inverse transforms of independent polynomials
 // --------------------------------------------------------------------------
 
-// Forward transforms by one workgroup of NP polynomials of one limb, p and p +
-// L (NP = 2: the two components of one ciphertext, p = (e 2 L + l)).  Output
+// Forward transform of polynomial p (limb p % L) by one workgroup.  Output
 // forms (split):
 //   0  uint64 residues, polynomial-major like the input;
 //   1  27-bit halves (uint2), polynomial-major: the form the 64-bit
@@ -54,7 +53,7 @@ __device__ __forceinline__ uint64_t mulmod(uint64_t a, uint64_t b, const Prime& 
 //      r = 2q + c (R = 2Q) for polynomial p = ((q d + i) 2 + c) L + l: each
 //      32-slot group of a row is one contiguous block over the coordinates,
 //      the form the digit transpose of the matrix-core schedule reads.
-template <int LOGN, int SPLIT, bool PM, int NP>
+template <int LOGN, int SPLIT, bool PM>
 __device__ __forceinline__ void ntt_fwd_poly(int p, int tid, uint64_t* lds,
                                              const uint64_t* __restrict__ in,
                                              uint64_t* __restrict__ out, int L,
@@ -63,70 +62,67 @@ __device__ __forceinline__ void ntt_fwd_poly(int p, int tid, uint64_t* lds,
   constexpr int N = NttShape<LOGN>::N;
   const int l = uniform(p % L);
   const Prime& P = ps.p[l];
-  uint64_t v[NP][16];
+  const uint64_t* src = in + (size_t)p * N;
+  uint64_t v[16];
   bool bad = false;
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
+  for (int a = 0; a < 16; ++a)
+    v[a] = __builtin_nontemporal_load(coef_ptr<LOGN, PM>(src, tid, a));  // read once
+  // every load is on its way before the first is looked at (one loop for both
+  // ran a quarter slower)
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int a = 0; a < 16; ++a)
-      v[j][a] = __builtin_nontemporal_load(
-          coef_ptr<LOGN, PM>(in + (size_t)(p + j * L) * N, tid, a));  // read once
-#pragma unroll
-  for (int j = 0; j < NP; ++j)
-#pragma unroll
-    for (int a = 0; a < 16; ++a) bad |= v[j][a] >= P.q;
+  for (int a = 0; a < 16; ++a) bad |= v[a] >= P.q;
   if (bad && err) atomicOr(err, 1u);
-  ntt_fwd<LOGN, PM, NP>(v, lds, tid, tws.tw[l], P);
+  ntt_fwd<LOGN, PM>(v, lds, tid, tws.tw[l], P);
+  uint64_t* dst = out + (size_t)p * N;
+  if constexpr (SPLIT == 2) {
+    const int c = (p / L) & 1, i = (p / (2 * L)) % d, q = p / (2 * L * d);
+    uint64_t* base = out + (((size_t)l * R + 2 * q + c) * (N / 32) * d + i) * 32;
 #pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const int pj = p + j * L;
-    uint64_t* dst = out + (size_t)pj * N;
-    if constexpr (SPLIT == 2) {
-      const int c = (pj / L) & 1, i = (pj / (2 * L)) % d, q = pj / (2 * L * d);
-      uint64_t* base = out + (((size_t)l * R + 2 * q + c) * (N / 32) * d + i) * 32;
-#pragma unroll
-      for (int a = 0; a < 16; ++a) {
-        const int s = ntt_slot<LOGN>(tid, a);
-        // read once, by the digit transpose
-        __builtin_nontemporal_store(v[j][a], base + (size_t)(s >> 5) * d * 32 + (s & 31));
-      }
-    } else if constexpr (SPLIT == 1) {
-#pragma unroll
-      for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[j][a]);
-    } else {
-#pragma unroll
-      for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = v[j][a];
+    for (int a = 0; a < 16; ++a) {
+      const int s = ntt_slot<LOGN>(tid, a);
+      // read once, by the digit transpose
+      __builtin_nontemporal_store(v[a], base + (size_t)(s >> 5) * d * 32 + (s & 31));
     }
+  } else if constexpr (SPLIT == 1) {
+#pragma unroll
+    for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = halves27(v[a]);
+  } else {
+#pragma unroll
+    for (int a = 0; a < 16; ++a) *ntt_ptr<LOGN, PM>(dst, tid, a) = v[a];
   }
 }
 
-// Waves per SIMD that the transform kernels are compiled for.  One polynomial
-// per workgroup: the largest of 4, 6 and 8 at which no form spills for that
-// log2 N.  A pair holds 32 residues per thread (about 104 registers), four
-// waves, which is also what two workgroups of whole-word exchange buffers (70
-// KB each at N = 8192) leave of a CU.
-constexpr int ntt_fwd_waves(int logn, int split, int np) {
-  if (np == 2) return 4;
+// Waves per SIMD the transform kernels are compiled for.  The PM forms fit
+// eight (64 registers) with no spills or a few words; at N >= 8192 that is the
+// fastest (47,232 inverse transforms with the mask: 1.84 ms at six waves, 1.70
+// at eight).  Smaller rings serve small databases, whose launches are a chain of
+// latencies rather than a stream: fewer waves leave registers for loads in
+// flight (10,000 points at N = 4096: the inverse 10 us at four waves, 18 at
+// eight, the forward 16 at six, 19 at eight).  The general forms: the largest of
+// 4, 6 and 8 that does not spill for that log2 N.
+constexpr int ntt_fwd_waves(int logn, int split, bool pm) {
+  if (pm) return logn >= 13 ? 8 : 6;
   return split == 2 && logn != 8 && logn != 9 && logn != 14 ? 8 : 6;
 }
-constexpr int intt_mask_waves(int logn, int np) {
-  return np == 2 || logn == 11 || logn == 12 || logn == 14 ? 4 : 6;
+constexpr int intt_mask_waves(int logn, bool pm) {
+  if (pm) return logn >= 13 ? 8 : 4;
+  return logn == 11 || logn == 12 || logn == 14 ? 4 : 6;
 }
 
-// NP = 1: one polynomial per workgroup.  NP = 2: both components of one
-// (ciphertext, limb), which share every twiddle (15 16-byte words per lane in
-// each of the last two passes, more than the 16 residues themselves) and whose
-// independent products interleave.  With the PM products at N = 8192, 64
-// queries of 128 coordinates: 1.63 ms (3.9 TB/s in and out), against 2.16 ms
-// one polynomial at a time and 1.98 ms for the general products.
-template <int LOGN, int SPLIT, int NP, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT, NP))
+// One polynomial per workgroup.  At N = 8192 with the PM products, 64 queries
+// of 128 coordinates: 1.40 ms (4.6 TB/s in and out, a plain copy reaches 5.1),
+// 1.98 ms with the general ones.  Two polynomials of a limb per workgroup,
+// sharing their twiddles, took 1.63 ms: 104 registers leave four waves per SIMD,
+// too few to hide the loads, exchanges and stores of one polynomial behind the
+// products of another.
+template <int LOGN, int SPLIT, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT, PM))
 k_ntt_fwd(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int L, PrimeSet ps,
           TwSet tws, uint32_t* err, int d, int R) {
   extern __shared__ uint64_t lds[];
-  const int b = blockIdx.x;
-  ntt_fwd_poly<LOGN, SPLIT, PM, NP>(NP == 2 ? uniform(b / L * 2 * L + b % L) : b, threadIdx.x, lds, in,
-                                    out, L, ps, tws, err, d, R);
+  ntt_fwd_poly<LOGN, SPLIT, PM>(blockIdx.x, threadIdx.x, lds, in, out, L, ps, tws, err, d, R);
 }
 
 // In-place inverse transform, result multiplied by N^-1 and in [0, q).
@@ -187,10 +183,10 @@ k_masks(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restrict
 // inverse transform of the products plus the norm-and-mask plaintext
 // --------------------------------------------------------------------------
 
-// Polynomials p and (NP = 2: both components of output m) p + L of ct_out, p =
-// (m 2 + c) L + l: INTT, times N^-1, and for c = 0 add Delta_l [norm - r]_t at
-// every coefficient (PM: both terms are added lazily and reduced once).
-template <int LOGN, bool PM, int NP>
+// Polynomial p = (m 2 + c) L + l of ct_out: INTT, times N^-1, and for c = 0
+// add Delta_l [norm - r]_t at every coefficient (PM: both terms are added
+// lazily and reduced once).
+template <int LOGN, bool PM>
 __device__ __forceinline__ void intt_mask_poly(int p, int tid, uint64_t* lds,
                                                uint64_t* __restrict__ ct,
                                                const uint32_t* __restrict__ share,
@@ -201,14 +197,11 @@ __device__ __forceinline__ void intt_mask_poly(int p, int tid, uint64_t* lds,
   const int l = uniform(p % L), c = uniform((p / L) & 1), m = uniform(p / (2 * L));
   const Prime& P = ps.p[l];
   uint64_t* buf = ct + (size_t)p * N;
-  uint64_t v[NP][16];
+  uint64_t v[16];
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
-#pragma unroll
-    for (int a = 0; a < 16; ++a)
-      v[j][a] = __builtin_nontemporal_load(ntt_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a));
-  ntt_inv<LOGN, PM, true, NP>(v, lds, tid, tws.tw[l] + N, P);
-  if (NP == 2 || c == 0) {
+  for (int a = 0; a < 16; ++a) v[a] = __builtin_nontemporal_load(ntt_ptr<LOGN, PM>(buf, tid, a));
+  ntt_inv<LOGN, PM, true>(v, lds, tid, tws.tw[l] + N, P);
+  if (c == 0) {
     int qi, k;
     work_pair_uniform(work, m, C, qi, k);
     const uint32_t* nrm = norms + (size_t)k * N;
@@ -219,50 +212,48 @@ __device__ __forceinline__ void intt_mask_poly(int p, int tid, uint64_t* lds,
       const uint32_t pn = *coef_ptr<LOGN, PM>(nrm, tid, a), rj = *coef_ptr<LOGN, PM>(r, tid, a);
       const uint32_t mv = pn >= rj ? pn - rj : pn + t - rj;
       if constexpr (PM)
-        v[0][a] += mul_pm32(mv, P.delta, pc);
+        v[a] += mul_pm32(mv, P.delta, pc);
       else
-        v[0][a] = addmod(v[0][a], shoup(mv, P.delta, P.deltap, P.q), P.q);
+        v[a] = addmod(v[a], shoup(mv, P.delta, P.deltap, P.q), P.q);
     }
   }
   __syncthreads();  // every thread has read its inputs before any overwrite
   const uint32_t pd = pm_delta(P.q);
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
-#pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      if constexpr (PM) v[j][a] = reduce_pm60(v[j][a] + 2 * P.q, pd, P.q);
-      __builtin_nontemporal_store(v[j][a], coef_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a));
-    }
+  for (int a = 0; a < 16; ++a) {
+    if constexpr (PM) v[a] = reduce_pm60(v[a] + 2 * P.q, pd, P.q);
+    __builtin_nontemporal_store(v[a], coef_ptr<LOGN, PM>(buf, tid, a));
+  }
 }
 
-// The output polynomials (NP = 1: polynomial p; NP = 2: both components of
-// output m at limb l, returned as the first's p = m 2 L + l) that workgroup b
-// of a grid of 8 ceil(n / 8) takes (n of them; -1 for the grid's padding).
-// Consecutive blocks go to the eight XCDs in turn, so block b is the (b /
-// 8)-th of XCD b % 8, and each XCD takes a contiguous range of this order: for
-// all pairs (Qa > 0 queries, M = Qa C) chunk-major, the outputs of one chunk
-// for every query back to back, so that the chunk's norms are fetched once
-// into that XCD's L2; and the polynomials of an output adjacent, so that those
-// that read its mask row find it there.  A work list (Qa = 0) keeps its own
-// order.
-template <int NP>
+// The polynomial of ct_out that workgroup b of a grid of 8 ceil(n / 8) takes
+// (n = 2 L M polynomials; -1 for the grid's padding).  Consecutive blocks go
+// to the eight XCDs in turn, so block b is the (b / 8)-th of XCD b % 8, and
+// each XCD takes a contiguous range of this order: for all pairs (Qa > 0
+// queries, M = Qa C) chunk-major, the outputs of one chunk for every query
+// back to back, so that the chunk's norms are fetched once into that XCD's
+// L2; and the 2L polynomials of an output adjacent, so that the L that read
+// its mask row find it there.  A work list (Qa = 0) keeps its own order.
 __device__ __forceinline__ int intt_poly_of_block(int b, int n, int Qa, int C, int L) {
-  const int per = (n + 7) >> 3, W = NP == 2 ? L : 2 * L;
+  const int per = (n + 7) >> 3;
   const int idx = (b & 7) * per + (b >> 3);
   if (idx >= n) return -1;
-  const int r = idx / W;
-  return uniform((Qa <= 0 ? r : (r % Qa) * C + r / Qa) * 2 * L + idx % W);
+  if (Qa <= 0) return idx;
+  const int r = idx / (2 * L);
+  return uniform(((r % Qa) * C + r / Qa) * 2 * L + idx % (2 * L));
 }
 
-template <int LOGN, int NP, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, NP))
+// At N = 8192, 47,232 polynomials: 1.76 ms with the PM products, 2.13 ms with the
+// general ones.
+template <int LOGN, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM))
 k_intt_mask(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
             const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
             int L, uint32_t t, PrimeSet ps, TwSet tws, int n, int Qa) {
   extern __shared__ uint64_t lds[];
-  const int p = intt_poly_of_block<NP>(blockIdx.x, n, Qa, C, L);
+  const int p = intt_poly_of_block(blockIdx.x, n, Qa, C, L);
   if (p < 0) return;
-  intt_mask_poly<LOGN, PM, NP>(p, threadIdx.x, lds, ct, share, norms, work, C, L, t, ps, tws);
+  intt_mask_poly<LOGN, PM>(p, threadIdx.x, lds, ct, share, norms, work, C, L, t, ps, tws);
 }
 
 // --------------------------------------------------------------------------
@@ -400,62 +391,54 @@ k_cp_noise(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restr
 
 // k_intt_mask with the re-randomisation's coefficient-form terms (drawn by
 // k_cp_noise): e1, the flood and Delta [norm - r]_t on c0, e2 on c1.
-template <int LOGN, int NP, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, NP))
+template <int LOGN, bool PM>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM))
 k_intt_mask_cp(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
                const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
                int L, uint32_t t, const uint64_t* __restrict__ flood,
                const int8_t* __restrict__ errs, PrimeSet ps, TwSet tws, int n, int Qa) {
   extern __shared__ uint64_t lds[];
   constexpr int N = NttShape<LOGN>::N;
-  const int tid = threadIdx.x, p = intt_poly_of_block<NP>(blockIdx.x, n, Qa, C, L);
+  const int tid = threadIdx.x, p = intt_poly_of_block(blockIdx.x, n, Qa, C, L);
   if (p < 0) return;
-  const int l = uniform(p % L), c0 = uniform((p / L) & 1), m = uniform(p / (2 * L));
+  const int l = uniform(p % L), c = uniform((p / L) & 1), m = uniform(p / (2 * L));
   const Prime& P = ps.p[l];
   uint64_t* buf = ct + (size_t)p * N;
-  uint64_t v[NP][16];
+  uint64_t v[16];
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
+  for (int a = 0; a < 16; ++a) v[a] = *ntt_ptr<LOGN, PM>(buf, tid, a);
+  ntt_inv<LOGN, PM, true>(v, lds, tid, tws.tw[l] + N, P);
+  const int8_t* e = errs + ((size_t)m * 2 + c) * N;
 #pragma unroll
-    for (int a = 0; a < 16; ++a) v[j][a] = *ntt_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a);
-  ntt_inv<LOGN, PM, true, NP>(v, lds, tid, tws.tw[l] + N, P);
-  int qi, k;
-  work_pair_uniform(work, m, C, qi, k);
-  const uint32_t* nrm = norms + (size_t)k * N;
-  const uint32_t* r = share + (size_t)m * N;
-  const uint64_t* fl = flood + ((size_t)m * L + l) * N;
-  const PmConst pc = pm_const(P.q);
-  const uint32_t pd = pm_delta(P.q);
-#pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    const int8_t* e = errs + ((size_t)m * 2 + c0 + j) * N;
-#pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      const int x = e[coef_index<LOGN>(tid, a)];
-      v[j][a] = PM ? v[j][a] + (uint64_t)(int64_t)x : addmod(v[j][a], lift_small(x, P.q), P.q);
-    }
+  for (int a = 0; a < 16; ++a) {
+    const int x = e[coef_index<LOGN>(tid, a)];
+    v[a] = PM ? v[a] + (uint64_t)(int64_t)x : addmod(v[a], lift_small(x, P.q), P.q);
   }
-  if (NP == 2 || c0 == 0) {
+  if (c == 0) {
+    int qi, k;
+    work_pair_uniform(work, m, C, qi, k);
+    const uint32_t* nrm = norms + (size_t)k * N;
+    const uint32_t* r = share + (size_t)m * N;
+    const uint64_t* fl = flood + ((size_t)m * L + l) * N;
+    const PmConst pc = pm_const(P.q);
 #pragma unroll
     for (int a = 0; a < 16; ++a) {
-      const int jj = coef_index<LOGN>(tid, a);
-      const uint32_t pn = nrm[jj], rj = r[jj];
+      const int j = coef_index<LOGN>(tid, a);
+      const uint32_t pn = nrm[j], rj = r[j];
       const uint32_t mv = pn >= rj ? pn - rj : pn + t - rj;
-      const uint64_t fj = fl[jj];
       if constexpr (PM)
-        v[0][a] += mul_pm32(mv, P.delta, pc) + fj;
+        v[a] += mul_pm32(mv, P.delta, pc) + fl[j];
       else
-        v[0][a] = addmod(addmod(v[0][a], shoup(mv, P.delta, P.deltap, P.q), P.q), fj, P.q);
+        v[a] = addmod(addmod(v[a], shoup(mv, P.delta, P.deltap, P.q), P.q), fl[j], P.q);
     }
   }
   __syncthreads();  // every thread has read its inputs before any overwrite
+  const uint32_t pd = pm_delta(P.q);
 #pragma unroll
-  for (int j = 0; j < NP; ++j)
-#pragma unroll
-    for (int a = 0; a < 16; ++a) {
-      if constexpr (PM) v[j][a] = reduce_pm60(v[j][a] + 2 * P.q, pd, P.q);
-      *coef_ptr<LOGN, PM>(buf + (size_t)j * L * N, tid, a) = v[j][a];
-    }
+  for (int a = 0; a < 16; ++a) {
+    if constexpr (PM) v[a] = reduce_pm60(v[a] + 2 * P.q, pd, P.q);
+    *coef_ptr<LOGN, PM>(buf, tid, a) = v[a];
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -1194,7 +1177,7 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
     const int tk = uniform(s_ticket);
     if (tk >= n1) break;
     if (tk < n_ntt) {
-      ntt_fwd_poly<LOGN, 1, PM, 1>(tk, tid, lds, A.ct_in, A.qntt, L, ps, tws, A.err);
+      ntt_fwd_poly<LOGN, 1, PM>(tk, tid, lds, A.ct_in, A.qntt, L, ps, tws, A.err);
       ++done_ntt;
     } else {
       const int m = tk - n_ntt;
@@ -1276,7 +1259,7 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
     __syncthreads();
     const int tk = uniform(s_ticket);
     if (tk >= n3) break;
-    intt_mask_poly<LOGN, PM, 1>(tk, tid, lds, A.ct_out, A.share, A.norms, A.work, A.C, L, A.t, ps, tws);
+    intt_mask_poly<LOGN, PM>(tk, tid, lds, A.ct_out, A.share, A.norms, A.work, A.C, L, A.t, ps, tws);
   }
 }
 
@@ -1403,13 +1386,12 @@ k_gather32(const uint32_t* __restrict__ pts, long n, int d,
 }
 
 // Workgroup per (l, k, i) with k in [k0, k0 + nk): lift the signed plaintext
-// row mod q_l, forward NTT, store as 27-bit halves.  One polynomial per
-// workgroup: with next to nothing read, the stores of one workgroup overlap the
-// products of the others, and a pair of rows (128 registers and spills) was no
-// faster (9,600 rows of N = 8192: 0.225 ms, in pairs 0.259 ms; 0.329 ms with the
+// row mod q_l, forward NTT, store as 27-bit halves.  The stores of one workgroup
+// overlap the products of the others, which bound it; a pair of rows per
+// workgroup (128 registers and spills) was no faster (9,600 rows of N = 8192: 0.225 ms, in pairs 0.259 ms; 0.329 ms with the
 // general products).
 template <int LOGN, typename G, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, PM ? 6 : 4)
+__global__ void __launch_bounds__(NttShape<LOGN>::T, PM ? 8 : 4)
 k_encode_ntt(const G* __restrict__ gt, uint2* __restrict__ dbres, int k0, int nk, int C,
              int d, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
@@ -1777,50 +1759,20 @@ static void ntt_launch(K kern, unsigned grid, hipStream_t st, A... args) {
                      args...);
 }
 
-// Whether a launch over n polynomials takes them in pairs: built for the PM
-// products at N >= 4096, and only with at least two pairs for each of the 256
-// CUs.  Below that the launch is a chain of latencies, not a stream, and more
-// workgroups of half the work end sooner (the forward transform of 512
-// polynomials of N = 4096: 21 us one by one, 25 us in pairs; of 24,576 of N =
-// 8192: 0.97 ms one by one, 0.78 ms in pairs).
-static bool ntt_pairs(const PrimeSet& ps, int logN, long n) {
-  return ps.pm && logN >= 12 && n >= 4 * 256;
-}
-
-// Launches the pair form where ntt_pairs says so, else the single form, of a
-// kernel template <.., NP, PM>; n polynomials, the grid rounded up to a
-// multiple of `align`; `items` in the arguments is the number of workgroups
-// that have work.
-#define SANNS_NTT_NP(LG, n, align, kern, targs, ...)                                         \
-  do {                                                                                       \
-    const bool pairs_ = ntt_pairs(ps, LG, (n));                                              \
-    const int items = (int)(pairs_ ? ((n) + 1) / 2 : (n));                                   \
-    const unsigned grid_ = (unsigned)((items + (align)-1) / (align) * (align));              \
-    if (pairs_) {                                                                            \
-      if constexpr (LG >= 12)                                                                \
-        hipLaunchKernelGGL((kern<SANNS_UNPACK targs, 2, true>), dim3(grid_),                 \
-                           dim3(NttShape<LG>::T), NttShape<LG>::lds_bytes_pair, st, __VA_ARGS__); \
-    } else {                                                                                 \
-      ntt_launch<LG>(SANNS_PM(kern, SANNS_UNPACK targs, 1), grid_, st, __VA_ARGS__);         \
-    }                                                                                        \
-  } while (0)
-#define SANNS_UNPACK(...) __VA_ARGS__
-
 hipError_t launch_ntt_fwd(const uint64_t* in, uint64_t* out, int n_polys, int logN, int L,
                           const PrimeSet& ps, const TwSet& tws, uint32_t* err, int split,
                           hipStream_t st, int d, int R) {
   if (n_polys <= 0) return hipSuccess;
-  if (n_polys % (2 * L)) return hipErrorInvalidValue;  // whole ciphertexts
   if (split == 2 && (logN < 5 || d <= 0 || n_polys != R * d * L)) return hipErrorInvalidValue;
   switch (logN) {
 #define SANNS_CASE(LG)                                                                      \
   case LG:                                                                                  \
     if (split == 2)                                                                         \
-      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 2), in, out, L, ps, tws, err, d, R);     \
+      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 2), n_polys, st, in, out, L, ps, tws, err, d, R); \
     else if (split == 1)                                                                    \
-      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 1), in, out, L, ps, tws, err, d, R);     \
+      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 1), n_polys, st, in, out, L, ps, tws, err, d, R); \
     else                                                                                    \
-      SANNS_NTT_NP(LG, n_polys, 1, k_ntt_fwd, (LG, 0), in, out, L, ps, tws, err, d, R);     \
+      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 0), n_polys, st, in, out, L, ps, tws, err, d, R); \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1861,11 +1813,12 @@ hipError_t launch_intt_mask(uint64_t* ct, const uint32_t* share, const uint32_t*
                             const PrimeSet& ps, const TwSet& tws, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   const int n = M * 2 * L, Qa = work ? 0 : M / C;
+  const unsigned grid = (unsigned)((n + 7) / 8 * 8);
   switch (logN) {
 #define SANNS_CASE(LG)                                                                  \
   case LG:                                                                              \
-    SANNS_NTT_NP(LG, n, 8, k_intt_mask, (LG), ct, share, norms, work, C, L, t, ps, tws, \
-                 items, Qa);                                                            \
+    ntt_launch<LG>(SANNS_PM(k_intt_mask, LG), grid, st, ct, share, norms, work, C, L, t, \
+                   ps, tws, n, Qa);                                                     \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -2213,13 +2166,14 @@ hipError_t launch_intt_mask_cp(uint64_t* ct, const uint32_t* share, const uint32
   const long nf = (long)M * (N / 2);
   int8_t* errs = reinterpret_cast<int8_t*>(flood + (size_t)M * L * N);
   const int n = M * 2 * L, Qa = work ? 0 : M / C;
+  const unsigned grid = (unsigned)((n + 7) / 8 * 8);
   hipLaunchKernelGGL(k_cp_noise, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0, st, K, qids,
                      work, C, (long)M, N, L, cp, ds, ps, flood, errs);
   switch (logN) {
 #define SANNS_CASE(LG)                                                                     \
   case LG:                                                                                 \
-    SANNS_NTT_NP(LG, n, 8, k_intt_mask_cp, (LG), ct, share, norms, work, C, L, t,          \
-                 (const uint64_t*)flood, (const int8_t*)errs, ps, tws, items, Qa);         \
+    ntt_launch<LG>(SANNS_PM(k_intt_mask_cp, LG), grid, st, ct, share, norms, work, C, L, t, \
+                   (const uint64_t*)flood, (const int8_t*)errs, ps, tws, n, Qa);           \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE

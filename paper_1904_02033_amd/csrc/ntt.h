@@ -60,10 +60,6 @@ struct NttShape {
   static constexpr int inv_b(int j) { return j == P - 1 ? R : 4; }
   // exchanges go through LDS in two 32-bit halves
   static constexpr size_t lds_bytes = (size_t)(N + (N >> 4)) * sizeof(uint32_t);
-  // a pair of polynomials: whole words, one polynomial after the other (in
-  // halves at N = 16384, where the words would leave no room on a CU)
-  static constexpr bool pair_words = LOGN < 14;
-  static constexpr size_t lds_bytes_pair = lds_bytes * (pair_words ? 2 : 1);
 };
 
 __device__ __forceinline__ constexpr int lds_pad(int idx) { return idx + (idx >> 4); }
@@ -94,7 +90,7 @@ __device__ __forceinline__ int ntt_slot(int tid, int a) {
 // uniform address (kept as one by an empty asm statement) plus the thread's
 // 32-bit offset, so that 16 words cost no per-thread addresses.  (Left alone,
 // the compiler forms one 64-bit address per thread and word and keeps them
-// from the loads to the stores, 64 registers for a pair of polynomials.)  UNI:
+// from the loads to the stores.)  UNI:
 // the PM forms of whole wavefronts; the compiler does not take it in some of
 // the general ones.
 template <typename V>
@@ -182,9 +178,8 @@ __device__ __forceinline__ uint64_t lift_coef(int64_t x, uint64_t q) {
   return PM || x >= 0 ? (uint64_t)x : q - (uint64_t)(-x);
 }
 
-// NP polynomials of one limb share each twiddle.
-template <int LOGN, int B, int LO, bool PM, int NP>
-__device__ __forceinline__ void fwd_pass(uint64_t (&v)[NP][16], int tid,
+template <int LOGN, int B, int LO, bool PM>
+__device__ __forceinline__ void fwd_pass(uint64_t (&v)[16], int tid,
                                          const u64x2* __restrict__ tw, const Arith<PM>& A) {
 #pragma unroll
   for (int rp = B - 1; rp >= 0; --rp) {
@@ -199,13 +194,10 @@ __device__ __forceinline__ void fwd_pass(uint64_t (&v)[NP][16], int tid,
 #pragma unroll
         for (int l = 0; l < (1 << rp); ++l) {
           const int a = a0 | l, b = a | (1 << rp);
-#pragma unroll
-          for (int j = 0; j < NP; ++j) {
-            const uint64_t X = v[j][a];
-            const uint64_t Tm = A.mul(v[j][b], W);
-            v[j][a] = X + Tm;
-            v[j][b] = A.sub(X, Tm);
-          }
+          const uint64_t X = v[a];
+          const uint64_t Tm = A.mul(v[b], W);
+          v[a] = X + Tm;
+          v[b] = A.sub(X, Tm);
         }
       }
     }
@@ -220,8 +212,8 @@ __device__ __forceinline__ TwPtr<(LO == 0)> tw_inv_stage(const u64x2* tw, int ti
   return TwPtr<(LO == 0)>(tw, (1 << p) + (eidx<LOGN, B, LO>(tid, 0) & ((1 << p) - 1)));
 }
 
-template <int LOGN, int B, int LO, bool PM, int NP>
-__device__ __forceinline__ void inv_pass(uint64_t (&v)[NP][16], int tid,
+template <int LOGN, int B, int LO, bool PM>
+__device__ __forceinline__ void inv_pass(uint64_t (&v)[16], int tid,
                                          const u64x2* __restrict__ tw, const Arith<PM>& A) {
 #pragma unroll
   for (int rp = 0; rp < B; ++rp) {
@@ -235,20 +227,16 @@ __device__ __forceinline__ void inv_pass(uint64_t (&v)[NP][16], int tid,
 #pragma unroll
         for (int l = 0; l < (1 << rp); ++l) {
           const int a = a0 | l, b = a | (1 << rp);
-          u64x2 W;
-          if (p > 0) W = tb[eidx<LOGN, B, LO>(0, a) & ((1 << p) - 1)];
-#pragma unroll
-          for (int j = 0; j < NP; ++j) {
-            const uint64_t X = v[j][a], Y = v[j][b];
-            if (p == 0) {
-              // twiddle 1; inputs are below q
-              v[j][a] = X + Y;
-              v[j][b] = A.sub0(X, Y);
-            } else {
-              const uint64_t Tm = A.mul(Y, W);
-              v[j][a] = X + Tm;
-              v[j][b] = A.sub(X, Tm);
-            }
+          const uint64_t X = v[a], Y = v[b];
+          if (p == 0) {
+            // twiddle 1; inputs are below q
+            v[a] = X + Y;
+            v[b] = A.sub0(X, Y);
+          } else {
+            const u64x2 W = tb[eidx<LOGN, B, LO>(0, a) & ((1 << p) - 1)];
+            const uint64_t Tm = A.mul(Y, W);
+            v[a] = X + Tm;
+            v[b] = A.sub(X, Tm);
           }
         }
       }
@@ -284,87 +272,49 @@ __device__ __forceinline__ void lds_exchange(uint64_t (&v)[16], uint64_t* lds, i
     v[a] = lo[a] | ((uint64_t)ld[lds_pad(eidx<LOGN, B1, LO1>(0, a))] << 32);
 }
 
-// The same for a pair of polynomials, in whole 64-bit words through a buffer
-// of one polynomial: three barriers for both.
-template <int LOGN, int B0, int LO0, int B1, int LO1>
-__device__ __forceinline__ void lds_exchange_pair(uint64_t (&v)[2][16], uint64_t* lds, int tid) {
-  uint64_t* st = lds + lds_pad(eidx<LOGN, B0, LO0>(tid, 0));
-  const uint64_t* ld = lds + lds_pad(eidx<LOGN, B1, LO1>(tid, 0));
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    if (j) __syncthreads();
-#pragma unroll
-    for (int a = 0; a < 16; ++a) st[lds_pad(eidx<LOGN, B0, LO0>(0, a))] = v[j][a];
-    __syncthreads();
-#pragma unroll
-    for (int a = 0; a < 16; ++a) v[j][a] = ld[lds_pad(eidx<LOGN, B1, LO1>(0, a))];
-  }
-}
-
-template <int LOGN, int B0, int LO0, int B1, int LO1, int NP>
-__device__ __forceinline__ void exchange(uint64_t (&v)[NP][16], uint64_t* lds, int tid) {
-  if constexpr (NP == 2 && NttShape<LOGN>::pair_words) {
-    lds_exchange_pair<LOGN, B0, LO0, B1, LO1>(v, lds, tid);
-  } else {
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      if (j) __syncthreads();
-      lds_exchange<LOGN, B0, LO0, B1, LO1>(v[j], lds, tid);
-    }
-  }
-}
-
-template <int LOGN, int J, bool PM, int NP>
-__device__ __forceinline__ void fwd_from(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
+template <int LOGN, int J, bool PM>
+__device__ __forceinline__ void fwd_from(uint64_t (&v)[16], uint64_t* lds, int tid,
                                          const u64x2* __restrict__ tw, const Arith<PM>& A) {
   using S = NttShape<LOGN>;
   constexpr int LO = S::fwd_lo(J), B = S::fwd_b(J);
-  fwd_pass<LOGN, B, LO, PM, NP>(v, tid, tw, A);
+  fwd_pass<LOGN, B, LO, PM>(v, tid, tw, A);
   if constexpr (J + 1 < S::P) {
     // the barrier before the first store guards LDS still read by an
     // earlier transform of the workgroup
     if (J == 0) __syncthreads();
-    exchange<LOGN, B, LO, S::fwd_b(J + 1), S::fwd_lo(J + 1), NP>(v, lds, tid);
-    fwd_from<LOGN, J + 1, PM, NP>(v, lds, tid, tw, A);
+    lds_exchange<LOGN, B, LO, S::fwd_b(J + 1), S::fwd_lo(J + 1)>(v, lds, tid);
+    fwd_from<LOGN, J + 1, PM>(v, lds, tid, tw, A);
   }
 }
 
-template <int LOGN, int J, bool PM, int NP>
-__device__ __forceinline__ void inv_from(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
+template <int LOGN, int J, bool PM>
+__device__ __forceinline__ void inv_from(uint64_t (&v)[16], uint64_t* lds, int tid,
                                          const u64x2* __restrict__ tw, const Arith<PM>& A) {
   using S = NttShape<LOGN>;
   constexpr int LO = S::inv_lo(J), B = S::inv_b(J);
-  inv_pass<LOGN, B, LO, PM, NP>(v, tid, tw, A);
+  inv_pass<LOGN, B, LO, PM>(v, tid, tw, A);
   if constexpr (J + 1 < S::P) {
     if (J == 0) __syncthreads();
-    exchange<LOGN, B, LO, S::inv_b(J + 1), S::inv_lo(J + 1), NP>(v, lds, tid);
-    inv_from<LOGN, J + 1, PM, NP>(v, lds, tid, tw, A);
+    lds_exchange<LOGN, B, LO, S::inv_b(J + 1), S::inv_lo(J + 1)>(v, lds, tid);
+    inv_from<LOGN, J + 1, PM>(v, lds, tid, tw, A);
   }
 }
 
-// Forward transform of NP polynomials of one limb.  Input: residues below q
-// (PM: signed, |x| < 2^54), slot a = coefficient coef_index(tid, a).  Output:
-// slot a = evaluation a + 16 tid in [0, q).  lds holds NttShape<LOGN>::lds_bytes
-// (lds_bytes_pair for NP = 2); the caller synchronises before reusing it.
-template <int LOGN, bool PM, int NP>
-__device__ __forceinline__ void ntt_fwd(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
-                                        const u64x2* __restrict__ tw, const Prime& P) {
-  static_assert(LOGN <= 14, "forward values must stay within their bounds");
-  fwd_from<LOGN, 0, PM, NP>(v, lds, tid, tw, Arith<PM>(P.q));
-  const uint64_t nq = 0 - P.q;
-  const uint32_t pd = pm_delta(P.q);
-#pragma unroll
-  for (int j = 0; j < NP; ++j)
-#pragma unroll
-    for (int a = 0; a < 16; ++a)
-      v[j][a] = PM ? reduce_pm_signed(v[j][a], pd, P.q)
-                   : csub(csub(shoup_approx(v[j][a], 1, P.one, nq), 2 * P.q), P.q);
-}
-
+// Forward transform.  Input: residues below q (PM: signed, |x| < 2^54), slot
+// a = coefficient coef_index(tid, a).  Output: slot a = evaluation a + 16 tid
+// in [0, q).  lds holds NttShape<LOGN>::lds_bytes; the caller synchronises
+// before reusing it.
 template <int LOGN, bool PM>
 __device__ __forceinline__ void ntt_fwd(uint64_t (&v)[16], uint64_t* lds, int tid,
                                         const u64x2* __restrict__ tw, const Prime& P) {
-  ntt_fwd<LOGN, PM, 1>(reinterpret_cast<uint64_t(&)[1][16]>(v), lds, tid, tw, P);
+  static_assert(LOGN <= 14, "forward values must stay within their bounds");
+  fwd_from<LOGN, 0, PM>(v, lds, tid, tw, Arith<PM>(P.q));
+  const uint64_t nq = 0 - P.q;
+  const uint32_t pd = pm_delta(P.q);
+#pragma unroll
+  for (int a = 0; a < 16; ++a)
+    v[a] = PM ? reduce_pm_signed(v[a], pd, P.q)
+              : csub(csub(shoup_approx(v[a], 1, P.one, nq), 2 * P.q), P.q);
 }
 
 // Inverse transform.  Input: residues below q, slot a = evaluation a + 16 tid
@@ -373,35 +323,24 @@ __device__ __forceinline__ void ntt_fwd(uint64_t (&v)[16], uint64_t* lds, int ti
 // 2^54, 10.4 2^54), for callers that add terms before the reduction.  tw
 // points at the limb's inverse stage table, which is followed by the N pairs
 // of the final factor psi^-j N^-1.
-template <int LOGN, bool PM, bool LAZY, int NP>
-__device__ __forceinline__ void ntt_inv(uint64_t (&v)[NP][16], uint64_t* lds, int tid,
+template <int LOGN, bool PM, bool LAZY = false>
+__device__ __forceinline__ void ntt_inv(uint64_t (&v)[16], uint64_t* lds, int tid,
                                         const u64x2* __restrict__ tw, const Prime& P) {
   static_assert(LOGN <= 14, "inverse values must stay within their bounds");
   const Arith<PM> A(P.q);
-  inv_from<LOGN, 0, PM, NP>(v, lds, tid, tw, A);
+  inv_from<LOGN, 0, PM>(v, lds, tid, tw, A);
   const Vec2* F = reinterpret_cast<const Vec2*>(tw + NttShape<LOGN>::N);
   const uint32_t pd = pm_delta(P.q);
 #pragma unroll
   for (int a = 0; a < 16; ++a) {
     const Vec2 fv = *coef_ptr<LOGN, PM>(F, tid, a);
     const u64x2 f(fv.x, fv.y);
-#pragma unroll
-    for (int j = 0; j < NP; ++j) {
-      const uint64_t r = A.mul(v[j][a], f);
-      if constexpr (PM)
-        v[j][a] = LAZY ? r : reduce_pm60(r + 2 * P.q, pd, P.q);
-      else
-        v[j][a] = csub(csub(r, 2 * P.q), P.q);
-    }
-    // at most four factors (16 registers) in flight
-    if (NP > 1 && a % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    const uint64_t r = A.mul(v[a], f);
+    if constexpr (PM)
+      v[a] = LAZY ? r : reduce_pm60(r + 2 * P.q, pd, P.q);
+    else
+      v[a] = csub(csub(r, 2 * P.q), P.q);
   }
-}
-
-template <int LOGN, bool PM, bool LAZY = false>
-__device__ __forceinline__ void ntt_inv(uint64_t (&v)[16], uint64_t* lds, int tid,
-                                        const u64x2* __restrict__ tw, const Prime& P) {
-  ntt_inv<LOGN, PM, LAZY, 1>(reinterpret_cast<uint64_t(&)[1][16]>(v), lds, tid, tw, P);
 }
 
 }  // namespace sanns
