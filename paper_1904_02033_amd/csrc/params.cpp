@@ -119,7 +119,10 @@ std::vector<uint64_t> twiddle_table(uint32_t N, uint64_t q, uint64_t psi, bool p
   std::vector<uint64_t> t(6 * (size_t)N, 0);
   auto put = [&](size_t i, uint64_t w) {
     if (pm) {
-      pm_pair(w, (uint64_t)(((u128)w << 32) % q), &t[i]);
+      // w 2^32 mod q by 2^54 = delta, without a division
+      uint64_t w32 = (w >> 22) * pm_delta(q) + ((w & 0x3fffffull) << 32);
+      while (w32 >= q) w32 -= q;
+      pm_pair(w, w32, &t[i]);
     } else {
       t[i] = w;
       t[i + 1] = shoup_companion(w, q);
