@@ -290,8 +290,12 @@ __device__ __forceinline__ uint64_t flood_residue(const uint32_t* w, int b, uint
   const int bits = b + 1;
   const uint32_t pd = pm_delta(q);
   uint64_t r = 0;
-  for (int i = (bits - 1) >> 5; i >= 0; --i) {
+  // (unrolled over all eight words, so that w stays in registers: a loop from
+  // the top kept word puts it in LDS)
+#pragma unroll
+  for (int i = 7; i >= 0; --i) {
     const int keep = bits - 32 * i;
+    if (keep <= 0) continue;  // b is the same for every thread
     const uint32_t x = keep >= 32 ? w[i] : (w[i] & ((1u << keep) - 1u));
     if (pd) {
       r = reduce_pm60((uint64_t)(uint32_t)(r >> 22) * pd + ((r & 0x3fffffull) << 32) + x, pd, q);
