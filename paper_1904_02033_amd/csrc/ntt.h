@@ -17,9 +17,9 @@
 //   that the library derives): signed values, products by mul_pm (six
 //   multiply-adds, |T| < 10.4 2^54 for |x| < 2^62), butterflies X + T and
 //   X - T.  A stage adds at most 10.4 2^54, so after log2 N <= 14 stages
-//   values stay within 147 2^54 < 2^62.  Nine VALU instructions per butterfly
-//   against 17 for the general form: what bounds a transform is then its
-//   memory traffic and not its arithmetic.
+//   values stay within 147 2^54 < 2^62.  Nine or ten VALU instructions per
+//   butterfly against 17 for the general form (butterflies alone 3.3-3.6 T/s
+//   against 2.34 T/s): what bounds a transform is then its memory traffic.
 //   general: unsigned values, estimated Shoup quotients (products in [0, 4q)
 //   for any input below 2^63), butterflies X + T and X + 4q - T (the inverse's
 //   twiddle-free stage 0 maps inputs below q to values below 3q), below 58 q

@@ -1,15 +1,15 @@
-"""The launch rules' branches at the sizes where they change: transforms of
-polynomials in pairs or alone, one query against few chunks with the
-coordinates split over a workgroup's waves, point rows gathered 16, 4 or 1
-bytes at a time, decryption in batches, seeded encryption under primes away
-from 2^54, and the k-means kernels at the edges of their tiles.  Every value is
-an integer: equality throughout."""
+"""The launch rules' branches at the sizes where they change: many transforms of
+each ring degree against the persistent launch, one query against few chunks
+with the coordinates split over a workgroup's waves, the matrix-core schedule's
+row tiles of 16, 32 and 64, point rows gathered 16, 4 or 1 bytes at a time,
+decryption in batches, seeded encryption under primes away from 2^54, and the
+k-means kernels at the edges of their tiles.  Every value is an integer:
+equality throughout."""
 import numpy as np
 import pytest
 
 import oracle
 from oracle import balance as obal
-from problem import make_problem, true_distances
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -37,10 +37,10 @@ def _ctx(nat, stage, N, qs, t, flags=0):
     return stage.Context(params=p)
 
 
-def _seeded(nat, stage, N, L, n, d, Q, seed):
+def _seeded(nat, stage, N, L, n, d, Q, seed, flags=0):
     """A context, an encoded database and seeded queries, all on the device."""
     qs, t = oracle.rns_primes(N, L), oracle.plain_modulus(N, 27)
-    ctx = _ctx(nat, stage, N, qs, t)
+    ctx = _ctx(nat, stage, N, qs, t, flags)
     g = np.random.default_rng(seed)
     pts = g.integers(0, 256, (n, d)).astype(np.uint8)
     que = g.integers(0, 256, (Q, d)).astype(np.uint8)
@@ -71,11 +71,11 @@ def _check_distances(stage, ctx, sk, out, share, pts, que, slot, C):
         assert (tot[m][real] == oracle.sqdist(que[m // C], pts[ids[real]])).all(), m
 
 
-# 2 L Q d and 2 L Q C polynomials on both sides of 1,024, above it odd counts
-# of encoded rows too; the persistent form transforms one polynomial at a time
+# about a thousand polynomials and more in each direction; the persistent form
+# takes them from its own work queue
 @pytest.mark.parametrize("N,L,Q,d,C", [(4096, 2, 8, 33, 33), (8192, 3, 8, 23, 22),
                                        (16384, 4, 7, 19, 19), (4096, 2, 8, 31, 31)])
-def test_pair_transforms(mods, N, L, Q, d, C):
+def test_many_transforms(mods, N, L, Q, d, C):
     nat, stage = mods
     ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 5, d, Q, 10 + d)
     out, share = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED)
@@ -97,6 +97,26 @@ def test_split_coordinates_one_query(mods, N, L, d):
         assert torch.equal(share.view(torch.int32), gs.view(torch.int32))
         if L > 1:  # (one 54-bit prime does not hold the noise)
             _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+        ctx.close()
+
+
+# queries at both sides of each row tile, chunks at both sides of a column tile,
+# contractions of 32, 64, 96 and 128 coordinates (ragged ones too)
+@pytest.mark.parametrize("Q", [2, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("d", [5, 32, 50, 96, 128])
+def test_row_tiles(mods, Q, d):
+    nat, stage = mods
+    N, L = 256, 2
+    for C in (3, 65):
+        ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 9, d, Q, Q + d,
+                                                       nat.SANNS_FLAG_DIGIT_DB)
+        want = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED, (0, 0, 22))
+        for mode in (nat.SANNS_MODE_FUSED, nat.SANNS_MODE_BATCHED):
+            for lds in (nat.SANNS_SCHEDULE_MFMA, 0):  # forced, and as the model chooses
+                got = _run(stage, ctx, db, ct, ids, mode, (0, 0, lds))
+                assert torch.equal(got[0].view(torch.int64), want[0].view(torch.int64)), (C, lds)
+                assert torch.equal(got[1].view(torch.int32), want[1].view(torch.int32))
+        _check_distances(stage, ctx, sk, *got, pts, que, slot, C)
         ctx.close()
 
 
