@@ -70,7 +70,7 @@ k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restri
 // cycle per instruction, so the selection bounds it for d <= 128.  Centre
 // indices beyond 22 bits are taken in blocks, whose winners are compared in 64
 // bits.  At n = 200,000, d = 96, k = 2,000: 1.18 ms by 4-way dot products on the
-// vector units, 0.15 ms here.
+// vector units, 0.13 ms here.
 // (At least two waves per SIMD: with all 512 registers of one the compiler puts
 // the sums in the accumulation half and copies each out, 32 more instructions
 // for 64 candidates.)
