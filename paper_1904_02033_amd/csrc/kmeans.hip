@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 #include "kernels.h"
 #include "launch.h"
+#include "mfma.h"
 
 namespace sanns {
 
@@ -169,10 +170,10 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
         const v4i ng = *reinterpret_cast<const v4i*>(cng + ct + 4 * g);
         const v4i tag = *reinterpret_cast<const v4i*>(ctag + ct + 4 * g);
         // The products of all four tiles, step by step, then the selection of
-        // each: a product's successor in its sum is eight products away, and
-        // a sum is read long after its last product.  (Tile by tile, with the
-        // 32-coordinate product right behind the 64-coordinate one, the last
-        // tile's sums were read without it at 96 coordinates.)
+        // each: a product's successor in its sum is eight products away.  Where
+        // the last step is the 32-coordinate shape, mfma_shape_change keeps it
+        // clear of the 64-coordinate one (tile by tile, each right behind the
+        // other, half of the centres' sums were wrong at 96 coordinates).
         v4i hs[kKmTiles], ls[kKmTiles];
 #pragma unroll
         for (int t = 0; t < kKmTiles; ++t) {
@@ -186,7 +187,7 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
             hs[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ah[s], bx[t][s], hs[t], 0, 0, 0);
             ls[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(al[s], bx[t][s], ls[t], 0, 0, 0);
           }
-        __builtin_amdgcn_sched_barrier(0);
+        if (HALF && NS > 0) mfma_shape_change();
         if (HALF) {
 #pragma unroll
           for (int t = 0; t < kKmTiles; ++t) {

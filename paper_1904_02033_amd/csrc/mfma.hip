@@ -35,6 +35,7 @@
 #include <type_traits>
 #include "kernels.h"
 #include "launch.h"
+#include "mfma.h"
 #include "chacha.h"
 
 namespace sanns {
@@ -370,6 +371,7 @@ k_mac_mfma(const int8_t* __restrict__ qd, const int8_t* __restrict__ dbd, int R,
         load_a(pn, 0, a0);  // the next slot's step-0 fragments, behind step 1
       }
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (W0 != W1) mfma_shape_change();
       mfma_step(a1, 1, buf, acc);
       if (cq == 3) {
         __builtin_amdgcn_sched_barrier(0);

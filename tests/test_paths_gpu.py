@@ -245,3 +245,10 @@ def test_kmeans_update_many_points(mods, n):
     s = 127 * (n - 1) - 128
     assert C[0].tolist() == [(512 * s + n) // (2 * n)] * d and C[1].tolist() == [7] * d
     assert cnt.tolist() == [n, 0]
+
+
+# the widest rows of each contraction form, those whose sums hold products of two
+# shapes (d = 193 .. 224, as 65 .. 96 and 129 .. 160 above) among them
+@pytest.mark.parametrize("d", [80, 130, 161, 192, 193, 200, 224, 225])
+def test_kmeans_wide_rows(mods, d):
+    test_kmeans_tile_edges(mods, 513, d, 129)
