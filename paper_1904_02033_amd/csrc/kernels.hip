@@ -96,19 +96,34 @@ __device__ __forceinline__ void ntt_fwd_poly(int p, int tid, uint64_t* lds,
 
 // Waves per SIMD the transform kernels are compiled for.  The PM forms fit
 // eight (64 registers) with no spills or a few words; at N >= 8192 that is the
-// fastest (47,232 inverse transforms with the mask: 1.84 ms at six waves, 1.70
-// at eight).  Smaller rings serve small databases, whose launches are a chain of
-// latencies rather than a stream: fewer waves leave registers for loads in
-// flight (10,000 points at N = 4096: the inverse 10 us at four waves, 18 at
-// eight, the forward 16 at six, 19 at eight).  The general forms: the largest of
-// 4, 6 and 8 that does not spill for that log2 N.
-constexpr int ntt_fwd_waves(int logn, int split, bool pm) {
-  if (pm) return logn >= 13 ? 8 : 6;
+// fastest for a launch that streams (47,232 inverse transforms with the mask: 1.75
+// ms at six waves, 1.60 at eight).  A launch of few polynomials is a chain of
+// latencies instead, and fewer waves leave registers for loads in flight: FEW, see
+// ntt_few, and every launch of a smaller ring (10,000 points at N = 4096: the
+// inverse 10 us at four waves, 18 at eight, the forward 16 at six, 19 at eight).
+// The general forms: the largest of 4, 6 and 8 that spilled nothing for that log2
+// N when they were chosen; the forward digit form now spills 5 words at log2 N =
+// 10 and 6 at 12, and is 1% and 6% faster than it was without.
+constexpr int ntt_fwd_waves(int logn, int split, bool pm, bool few) {
+  if (pm) return logn >= 13 && !few ? 8 : 6;
   return split == 2 && logn != 8 && logn != 9 && logn != 14 ? 8 : 6;
 }
-constexpr int intt_mask_waves(int logn, bool pm) {
-  if (pm) return logn >= 13 ? 8 : 4;
+constexpr int intt_mask_waves(int logn, bool pm, bool few) {
+  if (pm) return logn >= 13 && !few ? 8 : 4;
   return logn == 11 || logn == 12 || logn == 14 ? 4 : 6;
+}
+
+// Launches of n polynomials that take the FEW forms (N >= 8192, PM): those whose
+// workgroups are all on the 256 CUs at once at six waves per SIMD (three of 512
+// threads per CU, one of 1,024).  Measured, eight waves / FEW: N = 8192, inverse
+// with the mask, n = 12: 25 / 16 us, 360: 28.5 / 23.1, 738: 44.7 / 40.0, 1,968:
+// 86 / 87, 3,936: 158 / 166; forward, n = 96: 18.9 / 15.8 us, 768: 34 / 31, 1,536:
+// 53.7 / 53.3, 6,144: 174 / 171, 49,152 for the digits: 1,383 / 1,427; N = 16384,
+// inverse, n = 8: 32 / 23 us, 256: 35 / 29, 512: 51 / 52; forward, n = 256: 31 /
+// 28, 512: 42 / 48.
+template <int LOGN>
+static bool ntt_few(long n, const PrimeSet& ps) {
+  return LOGN >= 13 && ps.pm && n <= 256 * (1536 / NttShape<LOGN>::T);
 }
 
 // One polynomial per workgroup.  At N = 8192 with the PM products, 64 queries
@@ -117,8 +132,8 @@ constexpr int intt_mask_waves(int logn, bool pm) {
 // sharing their twiddles, took 1.63 ms: 104 registers leave four waves per SIMD,
 // too few to hide the loads, exchanges and stores of one polynomial behind the
 // products of another.
-template <int LOGN, int SPLIT, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT, PM))
+template <int LOGN, int SPLIT, bool PM, bool FEW>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, ntt_fwd_waves(LOGN, SPLIT, PM, FEW))
 k_ntt_fwd(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int L, PrimeSet ps,
           TwSet tws, uint32_t* err, int d, int R) {
   extern __shared__ uint64_t lds[];
@@ -245,8 +260,8 @@ __device__ __forceinline__ int intt_poly_of_block(int b, int n, int Qa, int C, i
 
 // At N = 8192, 47,232 polynomials: 1.76 ms with the PM products, 2.13 ms with the
 // general ones.
-template <int LOGN, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM))
+template <int LOGN, bool PM, bool FEW>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM, FEW))
 k_intt_mask(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
             const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
             int L, uint32_t t, PrimeSet ps, TwSet tws, int n, int Qa) {
@@ -395,8 +410,8 @@ k_cp_noise(MaskKey K, const uint64_t* __restrict__ qids, const uint32_t* __restr
 
 // k_intt_mask with the re-randomisation's coefficient-form terms (drawn by
 // k_cp_noise): e1, the flood and Delta [norm - r]_t on c0, e2 on c1.
-template <int LOGN, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM))
+template <int LOGN, bool PM, bool FEW>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM, FEW))
 k_intt_mask_cp(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
                const uint32_t* __restrict__ norms, const uint32_t* __restrict__ work, int C,
                int L, uint32_t t, const uint64_t* __restrict__ flood,
@@ -1394,8 +1409,8 @@ k_gather32(const uint32_t* __restrict__ pts, long n, int d,
 // overlap the products of the others, which bound it; a pair of rows per
 // workgroup (128 registers and spills) was no faster (9,600 rows of N = 8192: 0.225 ms, in pairs 0.259 ms; 0.329 ms with the
 // general products).
-template <int LOGN, typename G, bool PM>
-__global__ void __launch_bounds__(NttShape<LOGN>::T, PM ? 8 : 4)
+template <int LOGN, typename G, bool PM, bool FEW>
+__global__ void __launch_bounds__(NttShape<LOGN>::T, PM && !FEW ? 8 : 4)
 k_encode_ntt(const G* __restrict__ gt, uint2* __restrict__ dbres, int k0, int nk, int C,
              int d, int L, PrimeSet ps, TwSet tws) {
   extern __shared__ uint64_t lds[];
@@ -1756,6 +1771,11 @@ k_add_plain(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,
 // The kernel's form for this context's primes (a context's twiddle tables are
 // built for the same choice).
 #define SANNS_PM(kern, ...) (ps.pm ? kern<__VA_ARGS__, true> : kern<__VA_ARGS__, false>)
+// The same for a launch of n polynomials of the kernels with a FEW form.
+#define SANNS_PM_N(n, kern, LG, ...)                                              \
+  (ntt_few<LG>(n, ps) ? kern<LG, ##__VA_ARGS__, true, (LG >= 13)>                 \
+                      : ps.pm ? kern<LG, ##__VA_ARGS__, true, false>              \
+                              : kern<LG, ##__VA_ARGS__, false, false>)
 
 template <int LG, typename K, typename... A>
 static void ntt_launch(K kern, unsigned grid, hipStream_t st, A... args) {
@@ -1772,11 +1792,14 @@ hipError_t launch_ntt_fwd(const uint64_t* in, uint64_t* out, int n_polys, int lo
 #define SANNS_CASE(LG)                                                                      \
   case LG:                                                                                  \
     if (split == 2)                                                                         \
-      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 2), n_polys, st, in, out, L, ps, tws, err, d, R); \
+      ntt_launch<LG>(SANNS_PM_N(n_polys, k_ntt_fwd, LG, 2), n_polys, st, in, out, L, ps, \
+                     tws, err, d, R);                                                   \
     else if (split == 1)                                                                    \
-      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 1), n_polys, st, in, out, L, ps, tws, err, d, R); \
+      ntt_launch<LG>(SANNS_PM_N(n_polys, k_ntt_fwd, LG, 1), n_polys, st, in, out, L, ps, \
+                     tws, err, d, R);                                                   \
     else                                                                                    \
-      ntt_launch<LG>(SANNS_PM(k_ntt_fwd, LG, 0), n_polys, st, in, out, L, ps, tws, err, d, R); \
+      ntt_launch<LG>(SANNS_PM_N(n_polys, k_ntt_fwd, LG, 0), n_polys, st, in, out, L, ps, \
+                     tws, err, d, R);                                                   \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
 #undef SANNS_CASE
@@ -1821,7 +1844,7 @@ hipError_t launch_intt_mask(uint64_t* ct, const uint32_t* share, const uint32_t*
   switch (logN) {
 #define SANNS_CASE(LG)                                                                  \
   case LG:                                                                              \
-    ntt_launch<LG>(SANNS_PM(k_intt_mask, LG), grid, st, ct, share, norms, work, C, L, t, \
+    ntt_launch<LG>(SANNS_PM_N(n, k_intt_mask, LG), grid, st, ct, share, norms, work, C, L, t, \
                    ps, tws, n, Qa);                                                     \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
@@ -2067,7 +2090,7 @@ static hipError_t launch_encode_ntt_t(const G* gt, uint2* dbres, int k0, int nk,
   switch (logN) {
 #define SANNS_CASE(LG)                                                                     \
   case LG:                                                                                 \
-    ntt_launch<LG>(SANNS_PM(k_encode_ntt, LG, G), (unsigned)(L * rows), st, gt, dbres, k0, nk, \
+    ntt_launch<LG>(SANNS_PM_N(L * rows, k_encode_ntt, LG, G), (unsigned)(L * rows), st, gt, dbres, k0, nk, \
                    C, d, L, ps, tws);                                                      \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)
@@ -2176,7 +2199,7 @@ hipError_t launch_intt_mask_cp(uint64_t* ct, const uint32_t* share, const uint32
   switch (logN) {
 #define SANNS_CASE(LG)                                                                     \
   case LG:                                                                                 \
-    ntt_launch<LG>(SANNS_PM(k_intt_mask_cp, LG), grid, st, ct, share, norms, work, C, L, t, \
+    ntt_launch<LG>(SANNS_PM_N(n, k_intt_mask_cp, LG), grid, st, ct, share, norms, work, C, L, t, \
                    (const uint64_t*)flood, (const int8_t*)errs, ps, tws, n, Qa);           \
     break;
     SANNS_LOGN_CASES(SANNS_CASE)

@@ -252,3 +252,24 @@ def test_kmeans_update_many_points(mods, n):
 @pytest.mark.parametrize("d", [80, 130, 161, 192, 193, 200, 224, 225])
 def test_kmeans_wide_rows(mods, d):
     test_kmeans_tile_edges(mods, 513, d, 129)
+
+
+# launches on both sides of the largest that take the transforms' form for few
+# polynomials (768 of N = 8192, 256 of N = 16384): forward 2 L d, inverse 2 L C,
+# encoding L d C
+@pytest.mark.parametrize("N,L,d,C", [(8192, 3, 128, 2), (8192, 3, 129, 2), (8192, 3, 2, 128),
+                                     (8192, 3, 2, 129), (16384, 2, 64, 2), (16384, 2, 65, 2),
+                                     (16384, 2, 2, 64), (16384, 2, 2, 65)])
+def test_few_transforms(mods, N, L, d, C):
+    nat, stage = mods
+    ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 5, d, 1, d + C)
+    out, share = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED)
+    po, psh = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_PERSISTENT)
+    assert torch.equal(out.view(torch.int64), po.view(torch.int64))
+    assert torch.equal(share.view(torch.int32), psh.view(torch.int32))
+    _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+    pk = stage.public_key(ctx, sk, 9).view(torch.int64)[None].contiguous().view(torch.uint64)
+    D = stage.Distances(ctx, db, 1, private=True)
+    out, share = D.run(ct, b"k" * 32, ids, pk=pk, flood_bits=20)
+    torch.cuda.synchronize()
+    _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
