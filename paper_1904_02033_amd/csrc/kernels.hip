@@ -1894,12 +1894,34 @@ hipError_t launch_mac_split(int ct, const uint2* qntt, const uint2* db, int d, i
 }
 
 // The largest tile whose workgroups are at least two for each of the 256 CUs
-// (else 1), and only while k_mac's own 1 x 8 tiles, in workgroups of 256 slots,
-// are not: from there on k_mac streams the database.
-int mac_split_tile(int logN, int C, int L) {
+// (else 1), where this form is the faster one.  k_mac's time is one thread's
+// chain of d loads for as long as its 1 x 8 workgroups (of 256 slots) find a CU
+// each, and a step longer beyond; this form's time is its work, in whole tiles of
+// four chunks, and from databases beyond the Infinity Cache it streams at 2.6
+// TB/s at most.  With the work counted in 1 x 8 workgroups, it is taken up to 180;
+// to 224 in rings of at most 4096, where more tiles share a slot range's query; to
+// 240 where k_mac has more than 256 workgroups; to 320 for at most 300 MB; under 32
+// coordinates, too short a chain to divide, to 96.  Whole calls, this form / k_mac
+// (us; work in brackets):
+//   8192 x 3 limbs, d = 96, 12 chunks (144): 100 / 130, 20 (240): 156 / 167, 28
+//   (336): 194 / 186, 40 (480): 252 / 214;  d = 128, 12 chunks: 139 / 153, 14
+//   (192): 169 / 159, 16: 179 / 163, 20 (240): 197 / 201;  d = 50, 24 chunks (288):
+//   100 / 116;  d = 16, 2 chunks (48): 41 / 49, 12 (144): 61 / 57
+//   16384 x 4, d = 128, 4 chunks (128): 196 / 197, 8 (256): 271 / 221
+//   4096 x 2, d = 128, 40 chunks (160): 107 / 125, 56 (224): 135 / 139, 60 (240):
+//   145 / 142;  d = 32, 80 chunks (320): 64 / 70, 120: 85 / 77
+//   2048 x 1, d = 64, 280 chunks (280): 91 / 97, 480: 143 / 118
+int mac_split_tile(int logN, int C, int L, int d) {
   if (logN < 6) return 0;
   const long N = 1l << logN;
-  if ((N < 256 ? 1 : N / 256) * ((C + 7) / 8) * L >= 512) return 0;
+  const long groups = (N < 256 ? 1 : N / 256) * ((C + 7) / 8) * L;
+  const long work = N * L * ((C + 3) / 4 * 4) / 2048;
+  const long most = d < 32                             ? 96
+                    : N * L * C * d * 8 <= 300000000 ? 320
+                    : groups > 256                   ? 240
+                    : N <= 4096                      ? 224
+                                                     : 180;
+  if (groups >= 512 || work > most) return 0;
   for (int ct = 4; ct > 1; ct /= 2)
     if ((N >> 6) * ((C + ct - 1) / ct) * L >= 512) return ct;
   return 1;

@@ -34,7 +34,7 @@ size_t mac_tile_bytes(int QT, int CT);  // 0 for a shape that is not built
 constexpr int kMacSplit = 90;  // + ct: the form's internal schedule id
 hipError_t launch_mac_split(int ct, const uint2* qntt, const uint2* db, int d, int L, int logN,
                             int C, const PrimeSet& ps, uint64_t* out, hipStream_t st);
-int mac_split_tile(int logN, int C, int L);
+int mac_split_tile(int logN, int C, int L, int d);
 
 // LDS-staged variants of the all-pairs multiply-accumulate:
 // X(id, QT, CT, QG, CG, S, DI, UNR), block = S slots x QG x CG threads

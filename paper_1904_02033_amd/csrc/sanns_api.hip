@@ -248,7 +248,8 @@ void choose_shape(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bool
     qt = 1;
     ct = 8;
     // few chunks: the split form (its tile replaces 1 x 8)
-    const int sp = regular && Q == 1 ? mac_split_tile(ctx->logN, (int)C, (int)ctx->p.L) : 0;
+    const int sp =
+        regular && Q == 1 ? mac_split_tile(ctx->logN, (int)C, (int)ctx->p.L, (int)d) : 0;
     if (sp) lds = kMacSplit + sp;
   } else {
     qt = 2;

@@ -273,3 +273,19 @@ def test_few_transforms(mods, N, L, d, C):
     out, share = D.run(ct, b"k" * 32, ids, pk=pk, flood_bits=20)
     torch.cuda.synchronize()
     _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+
+
+# both sides of the lines where one query goes from split coordinates to whole ones
+@pytest.mark.parametrize("N,L,d,C", [(8192, 3, 128, 12), (8192, 3, 128, 13), (8192, 3, 16, 8),
+                                     (8192, 3, 16, 9), (256, 1, 33, 2560), (256, 1, 33, 2561),
+                                     (8192, 3, 40, 24), (8192, 3, 40, 25),
+                                     (4096, 2, 128, 56), (4096, 2, 128, 57)])
+def test_split_coordinates_line(mods, N, L, d, C):
+    nat, stage = mods
+    ctx, db, sk, ct, ids, pts, que, slot = _seeded(nat, stage, N, L, C * N - 3, d, 1, d + C)
+    out, share = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED)
+    go, gs = _run(stage, ctx, db, ct, ids, nat.SANNS_MODE_FUSED, (1, 8))
+    assert torch.equal(out.view(torch.int64), go.view(torch.int64))
+    assert torch.equal(share.view(torch.int32), gs.view(torch.int32))
+    if L > 1:
+        _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
