@@ -129,6 +129,51 @@ namespace {
 void drop_profile_events(sanns_ctx* ctx);
 }
 
+namespace sanns {
+
+// Whether the matrix-core schedule is expected to beat the vector one for Q
+// queries against C chunks of dimension d.  Relative costs per (limb, slot),
+// from the kernels' times at Q = 64, C = 123, d = 128: the 64-bit vector
+// multiply-accumulate 8.6 ms (scales with Q C d); the matrix-core path's
+// digit transpose 1.35 ms (Q Dq), MFMA tiles 2.4 ms (64-row x 64-chunk tiles
+// x Dp, 4 of them) and sums transpose 1.25 ms (Q C).
+// With at most 16 queries (row tiles of 16 or 32, `small`) the tiles cost what
+// streaming the digits costs, 2.7 us per coordinate and 64-chunk tile, and 90 us
+// more with 32 rows; the vector schedule works in tiles of 4 queries x 16 chunks
+// and takes at least the time to stream its residues (0.75 ms), and its masks
+// are a launch of their own (0.61 ms).  Both sides measured at N = 8192, L = 3
+// (whole calls, vector / matrix-core): 123 chunks, d = 96, Q = 2: 0.67 / 0.76
+// ms, Q = 5: 1.18 / 1.01, Q = 9: 1.77 / 1.40, Q = 16: 2.53 / 2.07; d = 128, Q =
+// 3: 0.99 / 1.00, Q = 8: 1.70 / 1.50; d = 32, Q = 9: 0.89 / 0.94; 37 chunks, d =
+// 128, Q = 8: 0.72 / 0.82, Q = 16: 1.38 / 1.38; 13 chunks, d = 96, Q = 16: 0.64
+// / 1.02.  Two queries never gain: 128 chunks, d = 96: 0.63 / 0.76, d = 128: 0.81
+// / 0.90.  Neither does a call whose vector schedule is expected to take 40 us or
+// less, where the two launches more count: N = 256, L = 1, d = 96, 64 chunks, Q =
+// 5: 48 / 69 us, 300 chunks, Q = 12 (expected 33): 84 / 91; N = 2048, L = 1, d =
+// 64, 64 chunks, Q = 9 (33): 83 / 86, 100 chunks, Q = 5 (43): 88 / 77.
+bool mfma_expected_faster(uint32_t Q, uint32_t C, uint32_t d, uint32_t N, uint32_t L,
+                          bool small) {
+  const double Dp = mfma_padded_d((int)d), Dq = mfma_query_d((int)d);
+  const int rows = mfma_rows_per_tile((int)Q);
+  if (small && rows < 64) {
+    const double vtile = 8.6 * ((Q + 3) / 4 * 4) * ((C + 15) / 16 * 16) * (double)d / (64.0 * 128 * 128);
+    const double vector = std::max(vtile, 0.75 * C * (double)d / (123.0 * 128)) +
+                          0.61 * (double)Q * C / (64.0 * 123);
+    if (Q < 3 || vector * N * L / (8192.0 * 3) <= 0.04) return false;
+    const double tile = 0.0027 * Dp + (rows == 32 ? 0.09 : 0.0);
+    return 1.13 * Q * Dq / (64.0 * 128) + ((C + 63) / 64) * tile +
+               1.37 * (double)Q * C / (64.0 * 123) <
+           vector;
+  }
+  const double valu = 8.6 * (double)Q * C * d / (64.0 * 123 * 128);
+  const double tiles = (double)((2 * Q + 63) / 64) * ((C + 63) / 64);
+  const double mfma = 1.35 * Q * Dq / (64.0 * 128) + 2.4 * tiles * Dp / (4.0 * 128) +
+                      1.25 * (double)Q * C / (64.0 * 123);
+  return mfma < valu;
+}
+
+}  // namespace sanns
+
 namespace {
 
 int log2u(uint32_t x) {
@@ -179,41 +224,6 @@ bool db_has_digits(const sanns_ctx* ctx, uint32_t d) {
   return ctx->digit_db && mfma_supported(ctx->logN, (int)d);
 }
 
-// Whether the matrix-core schedule is expected to beat the vector one for Q
-// queries against C chunks of dimension d.  Relative costs per (limb, slot),
-// from the kernels' times at Q = 64, C = 123, d = 128: the 64-bit vector
-// multiply-accumulate 8.6 ms (scales with Q C d); the matrix-core path's
-// digit transpose 1.35 ms (Q Dq), MFMA tiles 2.4 ms (64-row x 64-chunk tiles
-// x Dp, 4 of them) and sums transpose 1.25 ms (Q C).
-// With at most 16 queries (row tiles of 16 or 32, `small`) the tiles cost what
-// streaming the digits costs, 2.7 us per coordinate and 64-chunk tile, and 90 us
-// more with 32 rows; the vector schedule works in tiles of 4 queries x 16 chunks
-// and takes at least the time to stream its residues (0.75 ms), and its masks
-// are a launch of their own (0.61 ms).  Both sides measured at N = 8192, L = 3
-// (whole calls, vector / matrix-core): 123 chunks, d = 96, Q = 2: 0.67 / 0.76
-// ms, Q = 5: 1.18 / 1.01, Q = 9: 1.77 / 1.40, Q = 16: 2.53 / 2.07; d = 128, Q =
-// 3: 0.99 / 1.00, Q = 8: 1.70 / 1.50; d = 32, Q = 9: 0.89 / 0.94; 37 chunks, d =
-// 128, Q = 8: 0.72 / 0.82, Q = 16: 1.38 / 1.38; 13 chunks, d = 96, Q = 16: 0.64
-// / 1.02.
-bool mfma_expected_faster(uint32_t Q, uint32_t C, uint32_t d, bool small) {
-  const double Dp = mfma_padded_d((int)d), Dq = mfma_query_d((int)d);
-  const int rows = mfma_rows_per_tile((int)Q);
-  if (small && rows < 64) {
-    const double vtile = 8.6 * ((Q + 3) / 4 * 4) * ((C + 15) / 16 * 16) * (double)d / (64.0 * 128 * 128);
-    const double vector = std::max(vtile, 0.75 * C * (double)d / (123.0 * 128)) +
-                          0.61 * (double)Q * C / (64.0 * 123);
-    const double tile = 0.0027 * Dp + (rows == 32 ? 0.09 : 0.0);
-    return 1.13 * Q * Dq / (64.0 * 128) + ((C + 63) / 64) * tile +
-               1.37 * (double)Q * C / (64.0 * 123) <
-           vector;
-  }
-  const double valu = 8.6 * (double)Q * C * d / (64.0 * 123 * 128);
-  const double tiles = (double)((2 * Q + 63) / 64) * ((C + 63) / 64);
-  const double mfma = 1.35 * Q * Dq / (64.0 * 128) + 2.4 * tiles * Dp / (4.0 * 128) +
-                      1.25 * (double)Q * C / (64.0 * 123);
-  return mfma < valu;
-}
-
 // Whether an all-pairs (or not) call of Q queries against C chunks runs the
 // matrix-core schedule: forced by sanns_set_schedule, or chosen by default on
 // a digit database when the cost model predicts it faster.  small = false (calls
@@ -224,7 +234,7 @@ bool call_uses_mfma(const sanns_ctx* ctx, uint32_t Q, uint32_t C, uint32_t d, bo
                     bool small = true) {
   if (!all_pairs || Q < 2 || !db_has_digits(ctx, d)) return false;
   if (ctx->force_lds > 0) return ctx->force_lds == kMfmaSchedule;
-  return mfma_expected_faster(Q, C, d, small);
+  return mfma_expected_faster(Q, C, d, ctx->p.N, ctx->p.L, small);
 }
 
 // mfma: an all-pairs call runs the matrix-core schedule (call_uses_mfma).

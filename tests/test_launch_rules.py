@@ -34,3 +34,26 @@ def test_one_query_form(lib, logn, L, d, C, split, tiles):
     f = lib["_ZN5sanns14mac_split_tileEiiii"]  # int mac_split_tile(logN, C, L, d)
     f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int] * 4
     assert (f(logn, C, L, d) > 0) == (split < tiles)
+
+
+# all pairs of at most 16 queries on a digit database: (N, limbs, d, chunks, queries,
+# time of the vector schedule, of the matrix-core schedule) of whole calls, in us
+SMALL_BATCH = [
+    (8192, 3, 96, 128, 2, 629, 757), (8192, 3, 128, 128, 2, 809, 896),
+    (8192, 3, 64, 128, 2, 542, 570), (4096, 2, 96, 128, 2, 249, 281),
+    (8192, 3, 96, 123, 8, 1309, 1161), (8192, 3, 64, 123, 6, 907, 813),
+    (8192, 3, 128, 140, 5, 1628, 1296), (8192, 3, 128, 37, 15, 1304, 1202),
+    (8192, 3, 96, 64, 9, 1036, 897), (4096, 2, 128, 64, 9, 411, 358),
+    (4096, 2, 96, 200, 12, 1043, 819), (16384, 4, 96, 60, 16, 3809, 3667),
+    (2048, 1, 64, 300, 5, 200, 155), (2048, 1, 64, 100, 5, 88, 77),
+    (2048, 1, 64, 64, 6, 65, 72), (2048, 1, 64, 64, 9, 83, 86),
+    (256, 1, 96, 64, 5, 48, 69), (256, 1, 96, 64, 16, 56, 75), (256, 1, 96, 300, 6, 69, 79),
+    (256, 1, 96, 300, 12, 84, 91), (256, 1, 96, 300, 15, 103, 99)]
+
+
+@pytest.mark.parametrize("N,L,d,C,Q,vector,matrix", SMALL_BATCH)
+def test_small_batch_schedule(lib, N, L, d, C, Q, vector, matrix):
+    # bool mfma_expected_faster(Q, C, d, N, L, small)
+    f = lib["_ZN5sanns20mfma_expected_fasterEjjjjjb"]
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_uint] * 5 + [ctypes.c_bool]
+    assert f(Q, C, d, N, L, True) == (matrix < vector)
