@@ -260,6 +260,16 @@ sanns_status sanns_decrypt_shares(sanns_ctx *ctx, const int8_t *sk,
 size_t sanns_distances_workspace(const sanns_ctx *ctx, const sanns_db *db,
                                  uint32_t Q, uint32_t M, int mode);
 
+/* The least workspace with which sanns_distances (circuit_private != 0:
+ * sanns_distances_cp) runs the same call.  Batches of 3 to 16 queries on a
+ * context with SANNS_FLAG_DIGIT_DB are where it can be less: they run faster on
+ * the matrix-core schedule, whose sums take several times the memory, and on the
+ * vector schedule, with the same outputs, if the workspace is smaller than
+ * sanns_distances_workspace() (sanns_distances_cp_workspace()). */
+size_t sanns_distances_workspace_min(const sanns_ctx *ctx, const sanns_db *db,
+                                     uint32_t Q, uint32_t M, int mode,
+                                     int circuit_private);
+
 /* The server's distance stage (Section 4.2; linear-scan protocol step 3,
  * with the norm and mask folded into the ciphertext): for each output m with
  * (query qi, chunk k),
@@ -283,7 +293,8 @@ size_t sanns_distances_workspace(const sanns_ctx *ctx, const sanns_db *db,
  *                 give bit-identical outputs
  *   ct_out        dev [M][2][L][N] uint64, coefficient form
  *   server_share  dev [M][N] uint32
- *   workspace     dev, at least sanns_distances_workspace() bytes
+ *   workspace     dev, sanns_distances_workspace() bytes, at least
+ *                 sanns_distances_workspace_min()
  * SANNS_MODE_BATCHED captures the launches into a hipGraph cached in the
  * context under the call's pointers and sizes and replays it on later calls
  * with the same ones (new contents of every device buffer, query_ids

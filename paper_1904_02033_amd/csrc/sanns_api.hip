@@ -742,13 +742,32 @@ extern "C" sanns_status sanns_decrypt_shares(sanns_ctx* ctx, const int8_t* sk,
 // server hot path
 // ===========================================================================
 
+namespace {
+
+// Workspace bytes of a call of M outputs (M = Q n_chunks: all pairs); small as in
+// call_uses_mfma.
+size_t distances_bytes(const sanns_ctx* ctx, const sanns_db* db, uint32_t Q, uint32_t M, int mode,
+                       bool cp, bool small) {
+  const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN && Q > 0 &&
+                    (uint64_t)M == (uint64_t)Q * db->n_chunks &&
+                    call_uses_mfma(ctx, Q, db->n_chunks, db->d, true, small);
+  return ws_layout(ctx, db->d, Q, M, mfma, cp).total;
+}
+
+}  // namespace
+
 extern "C" size_t sanns_distances_workspace(const sanns_ctx* ctx, const sanns_db* db,
                                             uint32_t Q, uint32_t M, int mode) {
   if (!ctx || !db) return 0;
-  const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN && Q > 0 &&
-                    (uint64_t)M == (uint64_t)Q * db->n_chunks &&
-                    call_uses_mfma(ctx, Q, db->n_chunks, db->d, true);
-  return ws_layout(ctx, db->d, Q, M, mfma).total;
+  return distances_bytes(ctx, db, Q, M, mode, false, true);
+}
+
+extern "C" size_t sanns_distances_workspace_min(const sanns_ctx* ctx, const sanns_db* db,
+                                                uint32_t Q, uint32_t M, int mode,
+                                                int circuit_private) {
+  if (!ctx || !db) return 0;
+  return std::min(distances_bytes(ctx, db, Q, M, mode, circuit_private != 0, true),
+                  distances_bytes(ctx, db, Q, M, mode, circuit_private != 0, false));
 }
 
 namespace {
@@ -937,13 +956,19 @@ sanns_status distances_impl(sanns_ctx* ctx, const sanns_db* db, const uint64_t* 
       if (work[2 * m] >= Q || work[2 * m + 1] >= C + tail.C)
         return fail(SANNS_E_RANGE, "work[%u] = (%u, %u) outside Q x n_chunks", m, work[2 * m],
                     work[2 * m + 1]);
-  const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN &&
-                    call_uses_mfma(ctx, Q, C, db->d, work == nullptr, !noalloc);
+  const bool may_mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN;
+  bool mfma = may_mfma && call_uses_mfma(ctx, Q, C, db->d, work == nullptr, !noalloc);
   const bool cp_on = pk != nullptr;
   if (cp_on && mode != SANNS_MODE_FUSED && mode != SANNS_MODE_BATCHED)
     return fail(SANNS_E_INVALID, "the circuit-private form runs in SANNS_MODE_FUSED or "
                                  "SANNS_MODE_BATCHED only");
-  const WsLayout W = ws_layout(ctx, db->d, Q, M, mfma, cp_on);
+  WsLayout W = ws_layout(ctx, db->d, Q, M, mfma, cp_on);
+  if (ws_bytes < W.total && may_mfma) {
+    // less than the matrix-core schedule of a small batch needs: the choice as if
+    // the batch were padded to 64 rows, whose workspace is often the smaller one
+    mfma = call_uses_mfma(ctx, Q, C, db->d, work == nullptr, false);
+    W = ws_layout(ctx, db->d, Q, M, mfma, cp_on);
+  }
   if (ws_bytes < W.total)
     return fail(SANNS_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, W.total);
   HIP_TRY(hipSetDevice(ctx->device));
@@ -1337,10 +1362,7 @@ extern "C" uint32_t sanns_flood_bits(const sanns_ctx* ctx) {
 extern "C" size_t sanns_distances_cp_workspace(const sanns_ctx* ctx, const sanns_db* db,
                                                uint32_t Q, uint32_t M, int mode) {
   if (!ctx || !db) return 0;
-  const bool mfma = mode != SANNS_MODE_PERSISTENT && mode != SANNS_MODE_PLAIN && Q > 0 &&
-                    (uint64_t)M == (uint64_t)Q * db->n_chunks &&
-                    call_uses_mfma(ctx, Q, db->n_chunks, db->d, true);
-  return ws_layout(ctx, db->d, Q, M, mfma, true).total;
+  return distances_bytes(ctx, db, Q, M, mode, true, true);
 }
 
 extern "C" sanns_status sanns_distances_cp(sanns_ctx* ctx, const sanns_db* db,

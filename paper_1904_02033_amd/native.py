@@ -44,6 +44,7 @@ EXPORTS = [
     "sanns_distances_cp_workspace", "sanns_flood_bits", "sanns_distances_gathered",
     "sanns_distances_gathered_workspace", "sanns_kmeans_workspace", "sanns_kmeans_init",
     "sanns_kmeans_assign", "sanns_kmeans_update", "sanns_slot_ranges",
+    "sanns_distances_workspace_min",
 ]
 SANNS_NOALLOC_SCRATCH_BYTES = 64 << 20
 SANNS_N_PHASES = 7
@@ -133,6 +134,9 @@ def load() -> ctypes.CDLL:
     L.sanns_decrypt_shares.restype = st
     L.sanns_distances_workspace.argtypes = [vp, ctypes.POINTER(sanns_db), u32, u32, i32]
     L.sanns_distances_workspace.restype = ctypes.c_size_t
+    L.sanns_distances_workspace_min.argtypes = [vp, ctypes.POINTER(sanns_db), u32, u32, i32,
+                                                i32]
+    L.sanns_distances_workspace_min.restype = ctypes.c_size_t
     L.sanns_distances.argtypes = [vp, ctypes.POINTER(sanns_db), vp, u32, ctypes.c_char_p,
                                   vp, vp, u32, i32, vp, vp, vp, ctypes.c_size_t, vp]
     L.sanns_distances.restype = st
@@ -295,6 +299,12 @@ def sanns_distances_noalloc(ctx: int, db: sanns_db, ct_in: int, Q: int, mask_key
 
 def sanns_distances_workspace(ctx: int, db: sanns_db, Q: int, M: int, mode: int) -> int:
     return load().sanns_distances_workspace(ctx, ctypes.byref(db), Q, M, mode)
+
+
+def sanns_distances_workspace_min(ctx: int, db: sanns_db, Q: int, M: int, mode: int,
+                                  circuit_private: bool = False) -> int:
+    return load().sanns_distances_workspace_min(ctx, ctypes.byref(db), Q, M, mode,
+                                                1 if circuit_private else 0)
 
 
 def sanns_distances(ctx: int, db: sanns_db, ct_in: int, Q: int, mask_key: bytes,

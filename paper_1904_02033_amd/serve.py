@@ -23,7 +23,10 @@ keys), and ignores ids a request may carry.
 HBM admission counts everything the loop allocates on the device: the
 per-slot pools (workspace, concatenated query ciphertexts, and output
 buffers when outputs are released at completion) at their actual capacity,
-plus the per-launch outputs and query-id vectors of launches in flight.
+plus the per-launch outputs and query-id vectors of launches in flight.  A
+launch is given the workspace of its fastest schedule where its buffers then
+stay within a slot's share of the budget, and the least one it runs with (the
+same outputs from a slower schedule) otherwise.
 
 Latency is measured from a request's arrival to the moment its shares are
 ready on the device.
@@ -189,11 +192,14 @@ class Server:
         R = self.dbs[dbname]
         ctx = R.ctx
         db = self._desc(dbname, st)
-        return {"ws": nat.sanns_distances_workspace(ctx.handle, db.desc, Q, M, self.mode),
-                "ct": Q * db.d * 2 * ctx.L * ctx.N * 8 if n_jobs > 1 else 0,
-                "out": M * 2 * ctx.L * ctx.N * 8,
-                "share": M * ctx.N * 4,
-                "qd": (Q * 8 + 511) // 512 * 512}
+        s = {"ws": nat.sanns_distances_workspace(ctx.handle, db.desc, Q, M, self.mode),
+             "ct": Q * db.d * 2 * ctx.L * ctx.N * 8 if n_jobs > 1 else 0,
+             "out": M * 2 * ctx.L * ctx.N * 8,
+             "share": M * ctx.N * 4,
+             "qd": (Q * 8 + 511) // 512 * 512}
+        if sum(s.values()) > self.hbm_budget // self.max_inflight:
+            s["ws"] = nat.sanns_distances_workspace_min(ctx.handle, db.desc, Q, M, self.mode)
+        return s
 
     def _footprint(self, dbname: str, st: str, Q: int, M: int) -> int:
         """Bytes one job needs when it is launched alone on empty pools."""

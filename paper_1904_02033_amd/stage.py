@@ -161,7 +161,8 @@ class Distances:
                  workspace: Optional[torch.Tensor] = None,
                  out_buffers: Optional[tuple] = None, private: bool = False):
         """workspace: optional uint8 device tensor of at least the required
-        size, reused instead of a fresh allocation; out_buffers: optional
+        size (or the least one, sanns_distances_workspace_min), reused instead
+        of a fresh allocation; out_buffers: optional
         pair of uint8 device tensors that hold the ciphertext outputs and the
         shares (at least M 2 L N 8 and M N 4 bytes), likewise reused;
         private: size the workspace for the circuit-private form
@@ -175,6 +176,9 @@ class Distances:
         self.ws_bytes = size(ctx.handle, db.desc, Q, self.M, mode)
         if workspace is not None and workspace.numel() >= self.ws_bytes:
             self.ws = workspace[:self.ws_bytes]
+        elif workspace is not None and workspace.numel() >= nat.sanns_distances_workspace_min(
+                ctx.handle, db.desc, Q, self.M, mode, private):
+            self.ws, self.ws_bytes = workspace, workspace.numel()
         else:
             self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=dev)
         shape_out, shape_share = (self.M, 2, ctx.L, ctx.N), (self.M, ctx.N)

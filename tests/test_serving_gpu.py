@@ -201,3 +201,63 @@ def test_query_ids_are_never_reused(world):
                 k = (r.db if r.db != "C" else "C", int(q))
                 assert k not in seen, f"query id {int(q)} reused under database {r.db}"
                 seen[k] = r.rid
+
+
+def test_small_batch_within_the_former_budget(world):
+    """Nine queries on a digit database run fastest with a workspace several times
+    the vector schedule's; a budget that holds only the latter still serves them,
+    and the entry points take a workspace between the two, with the same outputs."""
+    nat, serve, stage = world["nat"], world["serve"], world["stage"]
+    N, L, C, d, Q = 1024, 2, 123, 96, 9
+    p = nat.sanns_params()
+    p.N, p.L, p.t = N, L, oracle.plain_modulus(N, 25)
+    for l, q in enumerate(oracle.rns_primes(N, L)):
+        p.q[l] = q
+    p.flags = nat.SANNS_FLAG_INSECURE_TEST | nat.SANNS_FLAG_DIGIT_DB
+    ctx = stage.Context(params=p)
+    g = np.random.default_rng(7)
+    n = C * N - 11
+    db = stage.encode_db(ctx, g.integers(0, 256, (n, d)).astype(np.uint8),
+                         stage.linear_slot_map(n, N, g.permutation(n)))
+    sk = stage.keygen(ctx, 1)
+    dev = lambda x: torch.as_tensor(x).cuda()
+    ct = stage.encrypt_query_seeded(ctx, sk, dev(g.integers(0, 256, (Q, d)).astype(np.int32)), 2)
+    key = synthdata.gen_mask_key(3)
+    qids = dev(np.arange(Q, dtype=np.uint64))
+    same = lambda a, b: (torch.equal(a[0].view(torch.int64), b[0].view(torch.int64))
+                         and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32)))
+
+    M = Q * C
+    pks = torch.stack([stage.public_key(ctx, sk, 5).view(torch.int64)] * Q).view(torch.uint64)
+    for private in (False, True):
+        full = (nat.sanns_distances_cp_workspace if private else nat.sanns_distances_workspace)(
+            ctx.handle, db.desc, Q, M, nat.SANNS_MODE_FUSED)
+        least = nat.sanns_distances_workspace_min(ctx.handle, db.desc, Q, M,
+                                                  nat.SANNS_MODE_FUSED, private)
+        assert least < full
+        args = dict(pk=pks, flood_bits=20) if private else {}
+        want = stage.Distances(ctx, db, Q, private=private).run(ct, key, qids, **args)
+        for mode in (nat.SANNS_MODE_FUSED, nat.SANNS_MODE_BATCHED):
+            for nbytes in (least, full - 1, full):
+                ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+                D = stage.Distances(ctx, db, Q, mode=mode, workspace=ws, private=private)
+                assert D.ws.data_ptr() == ws.data_ptr()
+                assert same(D.run(ct, key, qids, **args), want)
+        D.ws_bytes = least - 1
+        with pytest.raises(nat.SannsError):
+            D.run(ct, key, qids, **args)
+
+    R = serve.ResidentDB("D", ctx, db=db, key=key)
+    budget = (nat.sanns_distances_workspace_min(ctx.handle, db.desc, Q, M, nat.SANNS_MODE_FUSED)
+              + M * 2 * L * N * 8 + M * N * 4 + 512)
+    want = stage.Distances(ctx, db, Q).run(ct, key, qids)
+    torch.cuda.synchronize()
+    for hbm in (budget, 3 * budget, 16 * budget):
+        R.next_qid = 0
+        server = serve.Server([R], hbm_budget=hbm)
+        reqs = server.run([serve.Request(0, "D", ct, 10)], realtime=False)
+        assert reqs[0].error is None and server.peak_used <= hbm
+        assert same(reqs[0].outputs["scan"][:2], want)
+    with pytest.raises(serve.AdmissionError):
+        serve.Server([R], hbm_budget=budget - 1).submit(serve.Request(1, "D", ct, 10))
+    ctx.device_status()
