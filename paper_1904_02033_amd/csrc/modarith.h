@@ -147,7 +147,8 @@ __device__ __forceinline__ uint64_t mul_pm(uint64_t x, u64x2 W, const PmConst& c
   return pm_join(L, H, c);
 }
 
-// x w (mod q) for x < 2^32, in [0, 2^57).
+// x w (mod q) for x < 2^32, in [0, 2^57 + 2^54) (below 2^57 for x < 2^31, as every
+// plaintext is).
 __device__ __forceinline__ uint64_t mul_pm32(uint32_t x, uint64_t w, const PmConst& c) {
   const uint64_t H = mul32x32(x, (uint32_t)(w >> 24));
   const uint64_t r = mul32x32(x, (uint32_t)w & 0xffffffu) + (uint64_t)lo32(H) * c.c24;

@@ -204,6 +204,29 @@ def test_transform_products():
                 assert 0 <= r < 1 << 56 and r % q == a * b % q
 
 
+def test_product_by_a_word():
+    """mul_pm32 over its whole range: below 2^57 + 2^54 for x < 2^32, which a value
+    just past 2^57 nearly reaches, below 2^57 for x < 2^31; with the lazy inverse's
+    value, 2 q and a flood residue it stays where the reduction holds."""
+    unit = 1 << 54
+    top = 0
+    for q in _short_primes() + [unit - (1 << 17), unit - (1 << 22) + 1]:
+        rng = random.Random(q + 4)
+        ws = [0, 1, q - 1, (((1 << 29) + 1) << 24) | 0xFFFFFF, ((1 << 30) - 2) << 24 | 0xFFFFFF]
+        ws += [rng.randrange(q) for _ in range(30)]
+        xs = [0, 1, (1 << 31) - 1, (1 << 31) - 8, (1 << 32) - 1, (1 << 32) - 8]
+        xs += [rng.randrange(1 << 32) for _ in range(30)]
+        for w in ws:
+            for x in xs:
+                H = x * (w >> 24)
+                r = x * (w & 0xFFFFFF) + (H & 0xFFFFFFFF) * (1 << 24) + (H >> 32) * 4 * (unit - q)
+                assert r % q == x * w % q
+                assert r < ((1 << 57) if x < 1 << 31 else (1 << 57) + unit), (q, x, w)
+                top = max(top, r)
+    assert top > 1 << 57
+    assert 52 * unit // 5 + (1 << 57) + unit + 3 * unit < 1 << 60
+
+
 def test_workload_primes_take_the_short_forms():
     """The primes of every workload here (N = 4096 ... 16384, L <= 3) are
     2^54 - delta with delta < 2^22, so the batched schedules run the short

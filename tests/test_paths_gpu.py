@@ -289,3 +289,31 @@ def test_split_coordinates_line(mods, N, L, d, C):
     assert torch.equal(share.view(torch.int32), gs.view(torch.int32))
     if L > 1:
         _check_distances(stage, ctx, sk, out, share, pts, que, slot, C)
+
+
+def test_kmeans_centre_blocks(mods):
+    """More centres than a packed index holds (2^22): two blocks, whose winners are
+    compared in 64 bits; nearest centres in either, and equal ones in both, where the
+    lower index wins."""
+    nat, _ = mods
+    n, d, B = 70, 4, 1 << 22
+    k = B + 70
+    g = np.random.default_rng(22)
+    X = g.integers(-128, 128, (n, d)).astype(np.int8)
+    C = g.integers(-128 * 256, 127 * 256 + 1, (k, d)).astype(np.int32)
+    for i, js in enumerate([(100, B + 5), (B + 69,), (B - 1, B), (B + 64,), (0, B), (B - 1 - 64,),
+                            (B + 3, B + 66)]):
+        C[list(js)] = 256 * X[i].astype(np.int32)
+    C[B - 1] = 256 * X[2].astype(np.int32)
+    C[B] = C[B - 1]
+    Xd, Cd = _dev(X), _dev(C)
+    ws = torch.empty(nat.sanns_kmeans_workspace(k, d), dtype=torch.uint8, device="cuda")
+    a = torch.empty(n, dtype=torch.int32, device="cuda")
+    nat.sanns_kmeans_assign(Xd.data_ptr(), n, d, Cd.data_ptr(), k, 0, a.data_ptr(), 0,
+                            ws.data_ptr(), ws.numel(), 0)
+    c64 = C.astype(np.int64)
+    nrm = (c64 * c64).sum(1)
+    want = [int(np.argmin(nrm - 512 * (c64 @ x))) for x in X.astype(np.int64)]
+    got = a.cpu().numpy().tolist()
+    assert got == want
+    assert want[:4] == [100, B + 69, B - 1, B + 64] and want[6] == B + 3
