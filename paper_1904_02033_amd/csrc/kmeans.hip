@@ -5,7 +5,9 @@
 //               ties to the lower index.  <x, C_j> is an int8 matrix product
 //               of the points with the two signed base-256 digits of C_j (C =
 //               256 hi + lo, lo in [-128, 127]) on the matrix cores; every
-//               partial sum stays within int32 for d <= 256.
+//               partial sum stays within int32 for d <= 256.  A centre with a
+//               coordinate outside [-2^15, 2^15 - 129] (no mean of points is
+//               one) has no such digits and is compared by itself.
 //   update      centre j = floor(2^8 S_j / n_j + 1/2) from exact 64-bit
 //               sums (integer atomics, so the order of the additions does
 //               not matter); an empty cluster keeps its centre.
@@ -24,9 +26,9 @@ constexpr int kKmWgPoints = 4 * 16 * kKmTiles;  // points per workgroup (4 waves
 constexpr int kKmIdxBits = 22;     // centre index bits of a packed candidate
 
 // One wave per centre j: its digit words hi[w], then lo[w], w < dw <= 64 (4
-// coordinates per word, zero past d), and ||C_j||^2.  (A thread per centre,
-// walking its row alone, took 21 us for 2,000 centres of 96 coordinates; the
-// wave reads the row in one load.)
+// coordinates per word, zero past d), and ||C_j||^2; zero digits and -1 for one
+// beyond the digits' range.  (A thread per centre, walking its row alone, took 21
+// us for 2,000 centres of 96 coordinates; the wave reads the row in one load.)
 __global__ void __launch_bounds__(256)
 k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restrict__ packed,
           int64_t* __restrict__ cnorm) {
@@ -35,23 +37,28 @@ k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restri
   const int32_t* c = C + (size_t)j * d;
   uint32_t h = 0, l = 0;
   int64_t nrm = 0;
+  bool far = false;
   if (w < dw) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
       const int i = 4 * w + b;
       const int v = i < d ? c[i] : 0;
+      far |= v < -32768 || v > 32639;
       const int lv = ((v + 128) & 255) - 128;
       const int hv = (v - lv) / 256;
       l |= (uint32_t)(uint8_t)(int8_t)lv << (8 * b);
       h |= (uint32_t)(uint8_t)(int8_t)hv << (8 * b);
       nrm += (int64_t)v * v;
     }
-    packed[(size_t)j * 2 * dw + w] = (int32_t)h;
-    packed[(size_t)j * 2 * dw + dw + w] = (int32_t)l;
+  }
+  far = __any(far);
+  if (w < dw) {
+    packed[(size_t)j * 2 * dw + w] = far ? 0 : (int32_t)h;
+    packed[(size_t)j * 2 * dw + dw + w] = far ? 0 : (int32_t)l;
   }
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) nrm += __shfl_xor(nrm, s);
-  if (w == 0) cnorm[j] = nrm;
+  if (w == 0) cnorm[j] = far ? -1 : nrm;
 }
 
 // Closest centres on the int8 matrix cores.  A tile is 16 centres (rows) x 16
@@ -78,7 +85,7 @@ k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restri
 template <int DW>
 __global__ void __launch_bounds__(256, DW <= 24 ? 4 : DW <= 40 ? 3 : 2)
 k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
-            const int32_t* __restrict__ packed, const int64_t* __restrict__ cnorm, int k,
+            const int32_t* __restrict__ C, const int32_t* __restrict__ packed, const int64_t* __restrict__ cnorm, int k,
             const int32_t* __restrict__ prev, int32_t* __restrict__ assign,
             uint32_t* __restrict__ changed) {
   constexpr int NS = DW / 16;             // steps of 64 coordinates
@@ -133,6 +140,7 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
     if (tid < kKmStage && c0 + tid < k) ncn = cnorm[c0 + tid];
   };
   constexpr int kBlock = 1 << kKmIdxBits;
+  bool far = false;
   fetch(0);
   for (int k0 = 0; k0 < k; k0 += kBlock) {
     const int k1 = k - k0 < kBlock ? k : k0 + kBlock;
@@ -147,8 +155,10 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
         cw[e / RU * RS + e % RU] = nx[u];
       }
       if (tid < kKmStage) {
-        // padding centres never win: G = INT32_MIN, tag 0
-        const bool real = c0 + tid < k;
+        // padding centres and those beyond the digits' range never win: G =
+        // INT32_MIN, tag 0, the candidate that best[] starts from
+        const bool real = c0 + tid < k && ncn >= 0;
+        far |= c0 + tid < k && ncn < 0;
         cng[tid] = real ? -(int32_t)(ncn >> 9) : INT32_MIN;
         ctag[tid] = real ? ~(((uint32_t)ncn & 511u) << kKmIdxBits | (uint32_t)(c0 + tid - k0)) : 0u;
       }
@@ -217,7 +227,7 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
       b = o > b ? o : b;
       const uint32_t tag = ~(uint32_t)b;
       const int64_t key = (int64_t)(tag >> kKmIdxBits) - 512 * (int64_t)(int32_t)(b >> 32);
-      if (key < bkey[t]) {
+      if (b != INT64_MIN && key < bkey[t]) {
         bkey[t] = key;
         bidx[t] = k0 + (int)(tag & (kBlock - 1));
       }
@@ -229,6 +239,26 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
   for (int t = 1; t < kKmTiles; ++t) mine = g == t ? bidx[t] : mine;
   const long pt = base + 16 * g + m16;
   const bool in = pt < n;
+  if (__syncthreads_or(far)) {
+    // the centres beyond the digits' range, coordinate by coordinate
+    int64_t key0 = bkey[0];
+#pragma unroll
+    for (int t = 1; t < kKmTiles; ++t) key0 = g == t ? bkey[t] : key0;
+    __int128 key = key0 == INT64_MAX ? (__int128)1 << 100 : (__int128)key0;
+    const int8_t* row = X + (in ? pt : 0) * (long)d;
+    for (int j = 0; j < k; ++j) {
+      if (cnorm[j] >= 0) continue;
+      __int128 f = 0;
+      for (int i = 0; i < d; ++i) {
+        const int64_t c = C[(size_t)j * d + i];
+        f += c * (c - 512 * (int64_t)row[i]);
+      }
+      if (f < key || (f == key && j < mine)) {
+        key = f;
+        mine = j;
+      }
+    }
+  }
   if (prev && changed) {
     const uint64_t diff = __ballot(in && prev[in ? pt : 0] != mine);
     if (lane == 0 && diff) atomicAdd(changed, (uint32_t)__popcll(diff));
@@ -441,7 +471,7 @@ hipError_t launch_km_assign(const int8_t* X, long n, int d, const int32_t* C, in
   switch (dw) {
 #define SANNS_KM(DWV)                                                                       \
   case DWV:                                                                                 \
-    hipLaunchKernelGGL(k_km_assign<DWV>, dim3(grid), dim3(256), 0, st, X, n, d, words_ok,      \
+    hipLaunchKernelGGL(k_km_assign<DWV>, dim3(grid), dim3(256), 0, st, X, n, d, words_ok, C,   \
                        packed, cnorm, k, prev, assign, changed);                            \
     break;
     SANNS_KM(8) SANNS_KM(16) SANNS_KM(24) SANNS_KM(32) SANNS_KM(40) SANNS_KM(48) SANNS_KM(56)

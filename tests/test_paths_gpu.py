@@ -317,3 +317,37 @@ def test_kmeans_centre_blocks(mods):
     got = a.cpu().numpy().tolist()
     assert got == want
     assert want[:4] == [100, B + 69, B - 1, B + 64] and want[6] == B + 3
+
+
+@pytest.mark.parametrize("d", [1, 24, 96, 200])
+@pytest.mark.parametrize("far", [32640, -32769, 40000, 1 << 20, (1 << 31) - 1, -(1 << 31)])
+def test_kmeans_far_centres(mods, d, far):
+    """Centres beyond the points' grid (unused slots set far away, say): every int32
+    is a coordinate, alone, beside near centres, twice, and in all centres."""
+    nat, _ = mods
+    n, k = 300, 131
+    g = np.random.default_rng(d)
+    X = g.integers(-128, 128, (n, d)).astype(np.int8)
+    X[0], X[1] = -128, 127
+    C = g.integers(-128 * 256, 127 * 256 + 1, (k, d)).astype(np.int64)
+    some = C.copy()
+    some[[3, 70, 130]] = far
+    some[90, d // 2] = far
+    every = np.clip(C + far, -(1 << 31), (1 << 31) - 1)
+    every[60] = every[5]
+    one = np.clip(C[:1] + far, -(1 << 31), (1 << 31) - 1)
+    for cen in (some, every, one):
+        kk = len(cen)
+        Xd, Cd = _dev(X), _dev(cen.astype(np.int32))
+        ws = torch.empty(nat.sanns_kmeans_workspace(kk, d), dtype=torch.uint8, device="cuda")
+        a = torch.empty(n, dtype=torch.int32, device="cuda")
+        prev = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        changed = torch.zeros(1, dtype=torch.int32, device="cuda")
+        nat.sanns_kmeans_assign(Xd.data_ptr(), n, d, Cd.data_ptr(), kk, prev.data_ptr(),
+                                a.data_ptr(), changed.data_ptr(), ws.data_ptr(), ws.numel(), 0)
+        co = cen.astype(object)
+        nrm = (co * co).sum(1)
+        key = nrm[None, :] - 512 * (X.astype(object) @ co.T)
+        want = [int(np.argmin(r)) for r in key]
+        assert a.cpu().numpy().tolist() == want
+        assert int(changed) == n
