@@ -42,6 +42,10 @@ MFMA_I8_PEAK_TOPS = 5000.0  # dense int8 MFMA, MI355X
 HBM_PEAK_GBS = 8000.0
 
 
+DEVICE_SOURCES = ["kernels.hip", "mfma.hip", "kmeans.hip", "kernels.h", "mfma.h", "modarith.h",
+                  "ntt.h", "chacha.h"]
+
+
 def device_source_hash() -> str:
     """Hash of the device sources without their // comments and blank space,
     so that the recorded counters stay valid across comment edits and go
@@ -49,7 +53,7 @@ def device_source_hash() -> str:
     import hashlib
     import re
     h = hashlib.sha256()
-    for f in ["kernels.hip", "mfma.hip", "kernels.h", "modarith.h", "ntt.h", "chacha.h"]:
+    for f in DEVICE_SOURCES:
         with open(os.path.join(ROOT, "paper_1904_02033_amd", "csrc", f)) as fh:
             text = re.sub(r"//[^\n]*", "", fh.read())
         h.update(" ".join(text.split()).encode())
