@@ -7,6 +7,7 @@
 //   database norms     [C][N] uint32
 //   server shares      [M][N] uint32
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include "kernels.h"
 #include "launch.h"
 #include "ntt.h"
@@ -1286,6 +1287,9 @@ k_persistent(PersistArgs A, PrimeSet ps, TwSet tws) {
 // database encoding
 // --------------------------------------------------------------------------
 
+// Slots of a thread of k_gather<W>.
+__host__ __device__ constexpr int gather_slots(int W) { return W == 1 ? 1 : 2; }
+
 // W bytes of a point's row in one load (W = 16, 4 or 1).
 template <int W>
 struct RowBytes {
@@ -1307,53 +1311,57 @@ struct RowBytes<1> {
   __device__ __forceinline__ int get(int) const { return x; }
 };
 
-// Thread per two consecutive slots: gathers their points into the transposed
-// plaintext buffer gt[k][i][j] = -2 p[i] (int16, two slots per store) and
-// writes [||p||^2] to norms.  Slots [base, base + total) of the database; gt is
-// local to that range.  A point's row is read W bytes at a time (d % W == 0,
-// rows aligned to W): a
-// byte at a time the loads bound it (25 chunks of 128 coordinates 150 us; 16 bytes
-// at a time 25 us).
+// Thread per S consecutive slots: gathers their points into the transposed
+// plaintext buffer gt[k][i][j] = -2 p[i] (int16, S slots per store) and writes
+// [||p||^2] to norms.  Slots [base, base + total) of the database; gt is local to
+// that range.  A point's row is read W bytes at a time (d % W == 0, rows aligned to
+// W): a byte at a time the loads, a line for each lane, bound it (25 chunks of 128
+// coordinates 147 us; 16 bytes at a time 22 us).  Two slots per thread halve the
+// stores, but also the wavefronts that share those loads: with single bytes one
+// slot is the faster form (three chunks of 2,048 slots x 147 coordinates 22 us, two
+// slots 38; 25 chunks of 8,192 x 97 115 either way).
 template <int W>
 __global__ void __launch_bounds__(256)
 k_gather(const uint8_t* __restrict__ pts, int is_signed, long n, int d,
          const int64_t* __restrict__ slot_point, long base, long total, int logN,
          int16_t* __restrict__ gt, uint32_t* __restrict__ norms, uint32_t* err) {
-  const long g = 2 * ((long)blockIdx.x * blockDim.x + threadIdx.x);
+  constexpr int S = gather_slots(W);
+  const long g = S * ((long)blockIdx.x * blockDim.x + threadIdx.x);
   if (g >= total) return;  // total is a multiple of N
   const int N = 1 << logN;
   const long k = g >> logN;
   const int j = (int)(g & (N - 1));
-  const uint8_t* row[2];
-  bool real[2];
+  const uint8_t* row[S];
+  bool real[S];
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
+  for (int s = 0; s < S; ++s) {
     const long pid = slot_point[base + g + s];
     if ((pid >= n || pid < -1) && err) atomicOr(err, 2u);
     real[s] = pid >= 0 && pid < n;
     row[s] = pts + (real[s] ? (size_t)pid * d : 0);
   }
-  uint32_t* col = reinterpret_cast<uint32_t*>(gt + (size_t)k * d * N + j);
-  uint32_t nrm[2] = {0, 0};
+  typedef typename std::conditional<S == 2, uint32_t, uint16_t>::type Store;
+  Store* col = reinterpret_cast<Store*>(gt + (size_t)k * d * N + j);
+  uint32_t nrm[S] = {};
   for (int i0 = 0; i0 < d; i0 += W) {
-    RowBytes<W> v[2];
+    RowBytes<W> v[S];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) v[s].load(row[s] + i0);
+    for (int s = 0; s < S; ++s) v[s].load(row[s] + i0);
 #pragma unroll
     for (int b = 0; b < W; ++b) {
       uint32_t o = 0;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+      for (int s = 0; s < S; ++s) {
         const int u = real[s] ? v[s].get(b) : 0;
         const int x = is_signed ? (int)(int8_t)u : u;
         nrm[s] += (uint32_t)(x * x);
         o |= (uint32_t)(uint16_t)(int16_t)(-2 * x) << (16 * s);
       }
-      col[(size_t)(i0 + b) * (N / 2)] = o;
+      col[(size_t)(i0 + b) * (N / S)] = (Store)o;
     }
   }
-  norms[base + g] = nrm[0];
-  norms[base + g + 1] = nrm[1];
+#pragma unroll
+  for (int s = 0; s < S; ++s) norms[base + g + s] = nrm[s];
 }
 
 // Gathered chunks of secret-shared points: as k_gather, into 32-bit plaintext
@@ -2089,16 +2097,16 @@ hipError_t launch_gather(const void* pts, int is_signed, long n, int d,
                          int16_t* gt, uint32_t* norms, uint32_t* err, hipStream_t st) {
   if (total <= 0) return hipSuccess;
   const uint8_t* p = (const uint8_t*)pts;
-  const dim3 grid((unsigned)((total / 2 + 255) / 256));
+  auto grid = [&](int W) { return dim3((unsigned)((total / gather_slots(W) + 255) / 256)); };
   // the widest load that every row allows
   if (d % 16 == 0 && (uintptr_t)p % 16 == 0)
-    hipLaunchKernelGGL(k_gather<16>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
-                       total, logN, gt, norms, err);
+    hipLaunchKernelGGL(k_gather<16>, grid(16), dim3(256), 0, st, p, is_signed, n, d, slot_point,
+                       base, total, logN, gt, norms, err);
   else if (d % 4 == 0 && (uintptr_t)p % 4 == 0)
-    hipLaunchKernelGGL(k_gather<4>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
+    hipLaunchKernelGGL(k_gather<4>, grid(4), dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
                        total, logN, gt, norms, err);
   else
-    hipLaunchKernelGGL(k_gather<1>, grid, dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
+    hipLaunchKernelGGL(k_gather<1>, grid(1), dim3(256), 0, st, p, is_signed, n, d, slot_point, base,
                        total, logN, gt, norms, err);
   return hipGetLastError();
 }

@@ -351,3 +351,10 @@ def test_kmeans_far_centres(mods, d, far):
         want = [int(np.argmin(r)) for r in key]
         assert a.cpu().numpy().tolist() == want
         assert int(changed) == n
+
+
+# one slot per thread for rows read by bytes, two otherwise
+@pytest.mark.parametrize("dtype", [np.uint8, np.int8])
+@pytest.mark.parametrize("d", [1, 4, 9, 16, 36, 147])
+def test_gather_slots(mods, d, dtype):
+    test_gather_widths(mods, d, dtype)
