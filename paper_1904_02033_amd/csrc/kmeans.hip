@@ -164,7 +164,8 @@ k_km_assign(const int8_t* __restrict__ X, long n, int d, int words_ok,
       }
       __syncthreads();
       if (c0 + kKmStage < k) fetch(c0 + kKmStage);
-      for (int ct = 0; ct < kKmStage; ct += 16) {
+      const int nc = k1 - c0 < kKmStage ? k1 - c0 : kKmStage;
+      for (int ct = 0; ct < nc; ct += 16) {
         const char* ab = reinterpret_cast<const char*>(cw + (ct + m16) * RS);
         v4i ah[NS > 0 ? NS : 1], al[NS > 0 ? NS : 1];
         int64_t ahh = 0, alh = 0;
@@ -410,7 +411,7 @@ k_km_centers(const uint64_t* __restrict__ sums, const uint64_t* __restrict__ cou
   if (cnt == 0) return;
   int64_t S;
   if (paired) {
-    const int i = (int)(g % d);
+    const int i = (int)(g - (long)j * d);
     const uint64_t v = sums[(size_t)j * ((d + 1) / 2) + i / 2];
     S = (int64_t)(uint32_t)(i & 1 ? v >> 32 : v) - 128 * cnt;
   } else {
