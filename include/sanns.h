@@ -237,6 +237,9 @@ sanns_status sanns_public_key(sanns_ctx *ctx, const int8_t *sk, uint64_t seed,
  *   qnorm2        dev [M] uint32 = [||q||^2]_t of each ciphertext's query, or
  *                 NULL to return the decrypted message m itself
  *   client_share  dev [M][N] uint32
+ * Takes (1 + min(M, m0)) L N 8 bytes from the device's stream-ordered memory pool
+ * until the stream has passed the call, m0 the ciphertexts whose residues fill 64
+ * MiB (341 at N = 8192, L = 3; at least 1).
  * Errors: SANNS_E_INVALID, SANNS_E_DEVICE. */
 sanns_status sanns_decrypt_shares(sanns_ctx *ctx, const int8_t *sk,
                                   const uint64_t *ct, uint32_t M,
@@ -389,8 +392,9 @@ sanns_status sanns_kmeans_init(const int8_t *points, uint64_t n, uint32_t d,
                                uint32_t *bad, void *stream);
 
 /* Assignment step: assign[p] = argmin_j ||256 x_p - C_j||^2 over the k
- * centres (dev int32 [k][d]), ties to the lower index, into assign (dev int32
- * [n]).  With prev (dev int32 [n], may be NULL) and changed (dev uint32, may
+ * centres (dev int32 [k][d], any value; those with a coordinate outside [-2^15,
+ * 2^15 - 129], which no mean of points has, are compared one by one), ties to
+ * the lower index, into assign (dev int32 [n]).  With prev (dev int32 [n], may be NULL) and changed (dev uint32, may
  * be NULL), *changed is incremented by the number of points whose centre
  * differs from prev.  Errors: SANNS_E_INVALID, SANNS_E_WORKSPACE,
  * SANNS_E_DEVICE. */

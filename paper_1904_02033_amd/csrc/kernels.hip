@@ -97,14 +97,15 @@ __device__ __forceinline__ void ntt_fwd_poly(int p, int tid, uint64_t* lds,
 
 // Waves per SIMD the transform kernels are compiled for.  The PM forms fit
 // eight (64 registers) with no spills or a few words; at N >= 8192 that is the
-// fastest for a launch that streams (47,232 inverse transforms with the mask: 1.75
-// ms at six waves, 1.60 at eight).  A launch of few polynomials is a chain of
+// fastest for a launch that streams (47,232 inverse transforms with the mask: 1.76
+// ms at four waves, 1.61 at eight).  A launch of few polynomials is a chain of
 // latencies instead, and fewer waves leave registers for loads in flight: FEW, see
 // ntt_few, and every launch of a smaller ring (10,000 points at N = 4096: the
 // inverse 10 us at four waves, 18 at eight, the forward 16 at six, 19 at eight).
 // The general forms: the largest of 4, 6 and 8 that spilled nothing for that log2
-// N when they were chosen; the forward digit form now spills 5 words at log2 N =
-// 10 and 6 at 12, and is 1% and 6% faster than it was without.
+// N when they were chosen; now the forward digit form spills 6 words at log2 N =
+// 10 and 7 at 12 and the inverse 3 at 11, and whole calls of 64 queries there are 1
+// to 6% faster than before.
 constexpr int ntt_fwd_waves(int logn, int split, bool pm, bool few) {
   if (pm) return logn >= 13 && !few ? 8 : 6;
   return split == 2 && logn != 8 && logn != 9 && logn != 14 ? 8 : 6;
@@ -259,8 +260,8 @@ __device__ __forceinline__ int intt_poly_of_block(int b, int n, int Qa, int C, i
   return uniform(((r % Qa) * C + r / Qa) * 2 * L + idx % (2 * L));
 }
 
-// At N = 8192, 47,232 polynomials: 1.76 ms with the PM products, 2.13 ms with the
-// general ones.
+// At N = 8192, 47,232 polynomials: 1.61 ms with the PM products (1.69 within the
+// matrix-core step), 2.00 ms before them.
 template <int LOGN, bool PM, bool FEW>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM, FEW))
 k_intt_mask(uint64_t* __restrict__ ct, const uint32_t* __restrict__ share,

@@ -72,10 +72,11 @@ k_km_pack(const int32_t* __restrict__ C, int k, int d, int dw, int32_t* __restri
 //                                               low digits starts at -n_j),
 // among those the smallest r_j, then the smallest j.  A lane holds 4 centres of
 // a tile for one point and keeps the maximum of the 64-bit candidate (G, ~(r_j,
-// j)), four instructions per pair; the four lanes of a point are compared at
-// the end.  Per pair and 64 coordinates the products take a quarter of a
-// cycle of a SIMD's matrix core for each digit, the selection a quarter of a
-// cycle per instruction, so the selection bounds it for d <= 128.  Centre
+// j)), five instructions per pair (shift and add, a copy of the tag, compare, two
+// selects); the four lanes of a point are compared at the end.  Per pair and 64
+// coordinates the products take a quarter of a cycle of a SIMD's matrix core for
+// each digit, the selection a quarter of a cycle per instruction, so the selection
+// bounds it for d <= 128.  Centre
 // indices beyond 22 bits are taken in blocks, whose winners are compared in 64
 // bits.  At n = 200,000, d = 96, k = 2,000: 1.18 ms by 4-way dot products on the
 // vector units, 0.13 ms here.

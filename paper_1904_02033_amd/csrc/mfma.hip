@@ -236,7 +236,8 @@ __device__ __forceinline__ uint64_t fold_digit_sums_pm(const int32_t (&S)[13],
 // One MFMA step of the contraction: 64 coordinates (16 bytes per lane,
 // v_mfma_i32_16x16x64_i8) or 32 (8 bytes per lane, v_mfma_i32_16x16x32_i8,
 // lane l supplying row or column l % 16 and contraction bytes 8 (l / 16) ..
-// + 7; the output layout is that of the 64-wide form).
+// + 7; the output layout is that of the 64-wide form).  A contraction that ends
+// with the latter takes mfma_shape_change between the two.
 template <bool W32>
 struct StepFrag {
   typedef v4i T;

@@ -137,7 +137,8 @@ namespace sanns {
 // multiply-accumulate 8.6 ms (scales with Q C d); the matrix-core path's
 // digit transpose 1.35 ms (Q Dq), MFMA tiles 2.4 ms (64-row x 64-chunk tiles
 // x Dp, 4 of them) and sums transpose 1.25 ms (Q C).
-// With at most 16 queries (row tiles of 16 or 32, `small`) the tiles cost what
+// With at most 16 queries (row tiles of 16 or 32, `small`) a model of its own,
+// fitted to whole calls of such batches, not to the kernels above: the tiles cost what
 // streaming the digits costs, 2.7 us per coordinate and 64-chunk tile, and 90 us
 // more with 32 rows; the vector schedule works in tiles of 4 queries x 16 chunks
 // and takes at least the time to stream its residues (0.75 ms), and its masks
