@@ -492,10 +492,13 @@ hipError_t launch_km_update(const int8_t* X, long n, int d, const int32_t* assig
   uint64_t* counts = sums + (size_t)k * d;
   const long zc = (long)k * d + k;
   hipLaunchKernelGGL(k_km_zero, dim3((unsigned)((zc + 255) / 256)), dim3(256), 0, st, sums, zc);
-  const int paired = n < (1l << 32) / 255;
-  const long t = n * (paired ? (d + 1) / 2 : d);
-  int pairs = 0;
+  // two coordinates per add while their halves cannot carry; not for one or two
+  // coordinates by global adds, where a pair's denser lines queue longer than an add
+  // less is worth (n = 137,778, k = 1,966, d = 2: 28 us in pairs, 24 apart)
+  int pairs = 0, paired = n < (1l << 32) / 255;
   const int parts = paired ? km_accum_parts(n, d, k, &pairs) : 0;
+  if (parts == 0 && d <= 2) paired = 0;
+  const long t = n * (paired ? (d + 1) / 2 : d);
   const bool done =
       parts > 0 &&
       (pairs == 8   ? launch_km_accum_lds<8>(X, n, d, assign, k, parts, sums, counts, st)

@@ -358,3 +358,20 @@ def test_kmeans_far_centres(mods, d, far):
 @pytest.mark.parametrize("d", [1, 4, 9, 16, 36, 147])
 def test_gather_slots(mods, d, dtype):
     test_gather_widths(mods, d, dtype)
+
+
+# one and two coordinates apart, three in pairs, each with LDS tables where clusters
+# are large
+@pytest.mark.parametrize("d", [1, 2, 3])
+@pytest.mark.parametrize("n,k", [(3000, 400), (20000, 3)])
+def test_kmeans_update_narrow(mods, n, k, d):
+    nat, _ = mods
+    g = np.random.default_rng(n + d)
+    X = g.integers(-128, 128, (n, d)).astype(np.int8)
+    a = g.integers(0, k, n).astype(np.int32)
+    C = np.full((k, d), 7, dtype=np.int32)
+    Xd, Ad, Cd = _dev(X), _dev(a), _dev(C)
+    ws = torch.empty(nat.sanns_kmeans_workspace(k, d), dtype=torch.uint8, device="cuda")
+    nat.sanns_kmeans_update(Xd.data_ptr(), n, d, Ad.data_ptr(), k, Cd.data_ptr(), 0,
+                            ws.data_ptr(), ws.numel(), 0)
+    assert (Cd.cpu().numpy() == obal.update(X, a, C)).all()
