@@ -260,7 +260,7 @@ __device__ __forceinline__ int intt_poly_of_block(int b, int n, int Qa, int C, i
   return uniform(((r % Qa) * C + r / Qa) * 2 * L + idx % (2 * L));
 }
 
-// At N = 8192, 47,232 polynomials: 1.61 ms with the PM products (1.69 within the
+// At N = 8192, 47,232 polynomials: 1.61 ms with the PM products (1.69-1.74 within the
 // matrix-core step), 2.00 ms before them.
 template <int LOGN, bool PM, bool FEW>
 __global__ void __launch_bounds__(NttShape<LOGN>::T, intt_mask_waves(LOGN, PM, FEW))
